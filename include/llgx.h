@@ -135,7 +135,7 @@ void llgx_destroy(llgx_handle h);
 
 /* Sec. II, Eq. (2) and ref. [24]: compute the demagnetizing tensor N for
  * all cell offsets on the GPU in double precision (exact Newell form near,
- * moment expansion far), transform it with the library's FFT passes in
+ * Gauss quadrature far), transform it with the library's FFT passes in
  * double, and store the real k-space kernel in the working precision.
  * Idempotent.  Must precede any field or step call (else LLGX_E_STATE). */
 llgx_status llgx_precompute_demag(llgx_handle h);

@@ -1,5 +1,5 @@
 // Setup of the demagnetizing tensor of Eq. (2) in double precision: Newell's
-// closed forms (ref. [24]) near the origin, a moment expansion far away, and
+// closed forms (ref. [24]) near the origin, Gauss quadrature far away, and
 // the fold of its FFT into the real k-space kernel of the z pass.
 #include <hip/hip_runtime.h>
 
@@ -48,132 +48,154 @@ __device__ double newell_g(double x, double y, double z) {
     return sgn * t;
 }
 
-// 27-point second difference (weights 2, -1, -1 per axis) of the six
-// component functions, /(4 pi dx dy dz)
-__device__ void newell_exact(double X, double Y, double Z, double dx, double dy, double dz, double N[6]) {
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    for (int a = -1; a <= 1; ++a) {
-        const double wa = a == 0 ? 2.0 : -1.0;
-        const double x = X + a * dx;
-        for (int b = -1; b <= 1; ++b) {
-            const double wb = b == 0 ? 2.0 : -1.0;
-            const double y = Y + b * dy;
-            for (int c = -1; c <= 1; ++c) {
-                const double w = wa * wb * (c == 0 ? 2.0 : -1.0);
-                const double z = Z + c * dz;
-                acc[0] += w * newell_f(x, y, z);
-                acc[1] += w * newell_f(y, x, z);
-                acc[2] += w * newell_f(z, y, x);
-                acc[3] += w * newell_g(x, y, z);
-                acc[4] += w * newell_g(x, z, y);
-                acc[5] += w * newell_g(y, z, x);
-            }
-        }
+// Near offsets (R < Rs, see below): 27-point second difference (weights 2, -1,
+// -1 per axis) of the six component functions, /(4 pi dx dy dz).  32 lanes
+// take one offset: lane l < 27 evaluates the six functions at stencil point
+// l, then lane i < 6 adds the 27 values of component i in the order of the
+// points, so the sum rounds as a serial loop's does.  The work is a few
+// hundred offsets (those of the box nbx x nby x nbz around the origin) of 162
+// evaluations with an arctangent or two inverse hyperbolic sines each, a long
+// serial chain for one thread: with one thread per offset and the far field
+// in the same kernel the setup of a 32x32x2 mesh spent 1.45 ms here.
+constexpr int NEAR_GROUPS = NT / 32;
+__global__ __launch_bounds__(NT) void k_newell_near(int nx, int ny, int nz, int nbx, int nby, int nbz, double ux,
+                                                    double uy, double uz, double Rs, double* __restrict__ oct) {
+    __shared__ double val[NEAR_GROUPS][27][6];
+    const long n = (long)nx * ny * nz;
+    const int grp = threadIdx.x >> 5, l = threadIdx.x & 31;
+    const int id = (int)blockIdx.x * NEAR_GROUPS + grp;
+    const bool in = id < nbx * nby * nbz;
+    const int ix = id % nbx, iy = (id / nbx) % nby, iz = id / (nbx * nby);
+    const double X = ix * ux, Y = iy * uy, Z = iz * uz;
+    const bool on = in && sqrt(X * X + Y * Y + Z * Z) < Rs;
+    if (on && l < 27) {
+        const double x = X + (l / 9 - 1) * ux, y = Y + (l / 3 % 3 - 1) * uy, z = Z + (l % 3 - 1) * uz;
+        val[grp][l][0] = newell_f(x, y, z);
+        val[grp][l][1] = newell_f(y, x, z);
+        val[grp][l][2] = newell_f(z, y, x);
+        val[grp][l][3] = newell_g(x, y, z);
+        val[grp][l][4] = newell_g(x, z, y);
+        val[grp][l][5] = newell_g(y, z, x);
     }
-    const double s = 1.0 / (4.0 * M_PI * dx * dy * dz);
-    for (int i = 0; i < 6; ++i) N[i] = acc[i] * s;
+    __syncthreads();
+    if (on && l < 6) {
+        double acc = 0.0;
+        for (int q = 0; q < 27; ++q) {
+            const double w = (q / 9 == 1 ? 2.0 : -1.0) * (q / 3 % 3 == 1 ? 2.0 : -1.0) * (q % 3 == 1 ? 2.0 : -1.0);
+            acc += w * val[grp][q][l];
+        }
+        double N = acc * (1.0 / (4.0 * M_PI * ux * uy * uz));
+        // components odd along an axis vanish at zero offset along it
+        if ((ix == 0 && (l == 3 || l == 4)) || (iy == 0 && (l == 3 || l == 5)) || (iz == 0 && (l == 4 || l == 5)))
+            N = 0.0;
+        oct[l * n + ((long)iz * ny + iy) * nx + ix] = N;
+    }
 }
 
-// Far field: moment expansion of the cell-pair tensor,
-//   N_ij(R) = -(V/4 pi) sum_gamma m_gamma D^(gamma+e_i+e_j) (1/r),
-//   m_gamma = prod_a 2 d_a^g_a/(g_a+2)!  (even g_a, |gamma| <= 2K),
-// with D^k(1/r) = k! a_k and the Taylor coefficients a_k of 1/r generated
-// layer by layer (|k| = n) from
-//   n r^2 a_k = -(2n-1) sum_i x_i a_{k-e_i} - (n-1) sum_i a_{k-2e_i}.
-// The far form is used from R >= min(6 max(dx,dy,dz), 7 (dx dy dz)^(1/3)):
-// the float64 cancellation of the exact form grows with R in units of the
-// cube root of the cell volume, the truncation error of the expansion falls
-// with R in units of the longest side; with total moment order 14 both stay
-// near 1e-10 of V/(4 pi R^3) at the switch for cubes and for flat or
-// elongated cells.
-constexpr int FAR_K = 7;
-constexpr int FAR_N = 2 * FAR_K + 2;
+// Far field (R >= Rs): the cell-pair average of the dipole kernel,
+//   N_ij(R) = V/(4 pi) E_u[(r^2 delta_ij - 3 r_i r_j) / r^5], r = R + u,
+// with u the difference of two points drawn uniformly from a cell (per axis
+// the triangular distribution on [-d, d]), by the Gauss rule of that weight
+// per axis: n nodes integrate every moment of u through order 2n - 1 per
+// axis.  Nodes and weights: eigenvalues and first eigenvector components of
+// the Jacobi matrix of the moments 2/((k+1)(k+2)) (Golub and Welsch, Math.
+// Comp. 23 (1969) 221), computed with 60 digits.
+// The rule's error falls like (R + sqrt(R^2 - 1))^-2n (R in units of the
+// longest side).  Each rule is used from the R where its error reached
+// rounding (below 5e-15 of V/(4 pi R^3), against a 60-node rule, cells 1:1:1
+// to 1:1:0.05), the 8-node rule below R = 12 (2e-15 there at R = 6; at most
+// the truncation error of a moment expansion through order 14 everywhere).
+// Rs = min(6 max(dx,dy,dz), 7 (dx dy dz)^(1/3)): the float64 cancellation of
+// the exact form grows with R in units of the cube root of the cell volume,
+// the quadrature's error falls with R in units of the longest side.
+//
+// 4 lanes take one offset and split the x nodes.  Bound by FP64 arithmetic
+// (about 40 operations a node, 64 nodes for most offsets of a large mesh).
+// The moment expansion it replaces kept its three coefficient layers (459
+// doubles) in scratch memory: 256x256x16 14.7 ms, 160x80x8 2.48 ms.
 constexpr double FAR_SWITCH_SIDE = 6.0;
 constexpr double FAR_SWITCH_VOL = 7.0;
+constexpr int FAR_RULES = 5, FAR_MAXN = 8;
+struct FarRule {
+    int n;
+    double from;  // used from this R on
+    double u[FAR_MAXN], w[FAR_MAXN];
+};
+__constant__ const FarRule far_rules[FAR_RULES] = {
+    {3, 300.0,
+     {-0.6324555320336758664, 0.0, 0.6324555320336758664},
+     {0.20833333333333333333, 0.58333333333333333333, 0.20833333333333333333}},
+    {4, 60.0,
+     {-0.75092514330444738455, -0.26222984265274796383, 0.26222984265274796383, 0.75092514330444738455},
+     {0.098866304579875626786, 0.40113369542012437321, 0.40113369542012437321, 0.098866304579875626786}},
+    {5, 24.0,
+     {-0.82144059973838152787, -0.44992035245984196335, 0.0, 0.44992035245984196335, 0.82144059973838152787},
+     {0.051658257765490621791, 0.23947324070545739044, 0.41773700305810397554, 0.23947324070545739044,
+      0.051658257765490621791}},
+    {6, 12.0,
+     {-0.86573829497881909617, -0.5766148082484873353, -0.19426367677503889161, 0.19426367677503889161,
+      0.5766148082484873353, 0.86573829497881909617},
+     {0.029496561655309346531, 0.14748123370527284826, 0.32302220463941780521, 0.32302220463941780521,
+      0.14748123370527284826, 0.029496561655309346531}},
+    {8, 0.0,
+     {-0.91649860178182341063, -0.7301261104488862007, -0.46470084488963896783, -0.15462908084026113352,
+      0.15462908084026113352, 0.46470084488963896783, 0.7301261104488862007, 0.91649860178182341063},
+     {0.011529448606035851691, 0.062272586069543357121, 0.15758423371338039155, 0.26861373161104039964,
+      0.26861373161104039964, 0.15758423371338039155, 0.062272586069543357121, 0.011529448606035851691}}};
 
-__device__ __forceinline__ int lidx(int n, int i, int j) { return i * (n + 1) - (i * (i - 1)) / 2 + j; }
-
-__device__ void newell_far(double X, double Y, double Z, double dx, double dy, double dz, double N[6]) {
-    constexpr int LMAX = (FAR_N + 1) * (FAR_N + 2) / 2;
-    double lay[3][LMAX];  // layers n-2, n-1, n (rotating)
-    double fact[FAR_N + 1];
-    fact[0] = 1.0;
-    for (int i = 1; i <= FAR_N; ++i) fact[i] = fact[i - 1] * i;
-    double pm[3][FAR_K + 1];  // 2 d^(2q)/(2q+2)!
-    const double d[3] = {dx, dy, dz};
-    for (int a = 0; a < 3; ++a) {
-        double p = 1.0;
-        for (int q = 0; q <= FAR_K; ++q) {
-            pm[a][q] = 2.0 * p / fact[2 * q + 2];
-            p *= d[a] * d[a];
-        }
-    }
-    const double r2 = X * X + Y * Y + Z * Z;
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    int cur = 0, prev = 2, prev2 = 1;
-    lay[cur][0] = 1.0 / sqrt(r2);
-    for (int n = 1; n <= FAR_N; ++n) {
-        prev2 = prev;
-        prev = cur;
-        cur = (cur + 1) % 3;
-        for (int i = 0; i <= n; ++i) {
-            for (int j = 0; j <= n - i; ++j) {
-                const int l = n - i - j;
-                double s1 = 0.0, s2 = 0.0;
-                if (i >= 1) s1 += X * lay[prev][lidx(n - 1, i - 1, j)];
-                if (j >= 1) s1 += Y * lay[prev][lidx(n - 1, i, j - 1)];
-                if (l >= 1) s1 += Z * lay[prev][lidx(n - 1, i, j)];
-                if (n >= 2) {
-                    if (i >= 2) s2 += lay[prev2][lidx(n - 2, i - 2, j)];
-                    if (j >= 2) s2 += lay[prev2][lidx(n - 2, i, j - 2)];
-                    if (l >= 2) s2 += lay[prev2][lidx(n - 2, i, j)];
-                }
-                const double a = -((2 * n - 1) * s1 + (n - 1) * s2) / (n * r2);
-                lay[cur][lidx(n, i, j)] = a;
-                if (n < 2) continue;
-                const double da = a * fact[i] * fact[j] * fact[l];  // D^k (1/r)
-                const int k3[3] = {i, j, l};
-                // component (p,q): gamma = k - e_p - e_q must be even and non-negative
-                const int P[6] = {0, 1, 2, 0, 0, 1}, Q[6] = {0, 1, 2, 1, 2, 2};
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    int g[3] = {k3[0], k3[1], k3[2]};
-                    g[P[c]] -= 1;
-                    g[Q[c]] -= 1;
-                    if (g[0] < 0 || g[1] < 0 || g[2] < 0) continue;
-                    if ((g[0] | g[1] | g[2]) & 1) continue;
-                    acc[c] += pm[0][g[0] / 2] * pm[1][g[1] / 2] * pm[2][g[2] / 2] * da;
-                }
-            }
-        }
-    }
-    const double V = dx * dy * dz;
-    for (int c = 0; c < 6; ++c) N[c] = -V / (4.0 * M_PI) * acc[c];
-}
-
-__global__ void k_newell_octant(int nx, int ny, int nz, double dx, double dy, double dz, double* __restrict__ oct) {
+__global__ __launch_bounds__(NT) void k_newell_far(int nx, int ny, int nz, double ux, double uy, double uz, double Rs,
+                                                   double* __restrict__ oct) {
     const long n = (long)nx * ny * nz;
-    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
+    const long at = ((long)blockIdx.x * NT + threadIdx.x) >> 2;
+    const int part = threadIdx.x & 3;
+    const long idx = at < n ? at : n - 1;
     const int ix = (int)(idx % nx);
     const int iy = (int)((idx / nx) % ny);
     const int iz = (int)(idx / ((long)nx * ny));
-    // N is invariant under a common scaling of offsets and cell: use units of the largest side
-    const double s = fmax(dx, fmax(dy, dz));
-    const double ux = dx / s, uy = dy / s, uz = dz / s;
     const double X = ix * ux, Y = iy * uy, Z = iz * uz;
     const double R = sqrt(X * X + Y * Y + Z * Z);
-    const double Rs = fmin(FAR_SWITCH_SIDE, FAR_SWITCH_VOL * cbrt(ux * uy * uz));  // longest side = 1
-    double N[6];
-    if (R >= Rs)
-        newell_far(X, Y, Z, ux, uy, uz, N);
-    else
-        newell_exact(X, Y, Z, ux, uy, uz, N);
-    // components odd along an axis vanish at zero offset along it
-    if (ix == 0) N[3] = N[4] = 0.0;
-    if (iy == 0) N[3] = N[5] = 0.0;
-    if (iz == 0) N[4] = N[5] = 0.0;
-    for (int c = 0; c < 6; ++c) oct[c * n + idx] = N[c];
+    const bool on = R >= Rs;
+    if (!__any(on)) return;  // a whole wave of near offsets
+    // one rule for the wave: the one its nearest far offset needs
+    int rule = 0;
+    for (int q = 0; q + 1 < FAR_RULES; ++q)
+        if (__any(on && R < far_rules[q].from)) rule = q + 1;
+    const FarRule& fr = far_rules[rule];
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    for (int a = part; a < fr.n; a += 4) {
+        const double x = X + fr.u[a] * ux, wa = on ? fr.w[a] : 0.0, x2 = x * x;
+        for (int b = 0; b < fr.n; ++b) {
+            const double y = Y + fr.u[b] * uy, wb = wa * fr.w[b], s2 = x2 + y * y;
+            double e = 0.0, f = 0.0, fz = 0.0, fzz = 0.0;  // sums over z of w/r^3, 3 w/r^5, 3 w z/r^5, 3 w z^2/r^5
+            for (int c = 0; c < fr.n; ++c) {
+                const double z = on ? Z + fr.u[c] * uz : 1.0;
+                const double q = rsqrt(s2 + z * z), q2 = q * q;
+                const double i3 = fr.w[c] * q * q2, i5 = 3.0 * i3 * q2;
+                e += i3;
+                f += i5;
+                fz += i5 * z;
+                fzz += i5 * z * z;
+            }
+            acc[0] += wb * (e - x2 * f);
+            acc[1] += wb * (e - y * y * f);
+            acc[2] += wb * (e - fzz);
+            acc[3] -= wb * (x * y * f);
+            acc[4] -= wb * (x * fz);
+            acc[5] -= wb * (y * fz);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        acc[i] += __shfl_xor(acc[i], 1, 64);
+        acc[i] += __shfl_xor(acc[i], 2, 64);
+    }
+    if (!on || at >= n || part != 0) return;
+    const double s = ux * uy * uz / (4.0 * M_PI);
+    if (ix == 0) acc[3] = acc[4] = 0.0;
+    if (iy == 0) acc[3] = acc[5] = 0.0;
+    if (iz == 0) acc[4] = acc[5] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) oct[i * n + idx] = s * acc[i];
 }
 
 // place component comp of the octant at wrap-around indices of the padded
@@ -229,7 +251,19 @@ __global__ __launch_bounds__(NT) void k_fold(const cx<double>* __restrict__ spec
 hipError_t launch_newell_octant(hipStream_t s, int nx, int ny, int nz, double dx, double dy, double dz,
                                 double* octant) {
     const long n = (long)nx * ny * nz;
-    k_newell_octant<<<(unsigned)((n + 127) / 128), 128, 0, s>>>(nx, ny, nz, dx, dy, dz, octant);
+    // N is invariant under a common scaling of offsets and cell: use units of the largest side
+    const double m = std::fmax(dx, std::fmax(dy, dz));
+    const double ux = dx / m, uy = dy / m, uz = dz / m;
+    const double Rs = std::fmin(FAR_SWITCH_SIDE, FAR_SWITCH_VOL * std::cbrt(ux * uy * uz));  // longest side = 1
+    // the box that holds every offset with R < Rs (one more per axis than
+    // rounding of the products could leave out)
+    auto box = [&](int nn, double u) { return (int)std::fmin((double)nn, std::floor(Rs / u) + 2.0); };
+    const int bx = box(nx, ux), by = box(ny, uy), bz = box(nz, uz);
+    const long nbox = (long)bx * by * bz;
+    if (nbox > (1L << 30) || (4 * n + NT - 1) / NT > 0x7fffffffL) return hipErrorInvalidValue;
+    k_newell_near<<<(unsigned)((nbox + NEAR_GROUPS - 1) / NEAR_GROUPS), NT, 0, s>>>(nx, ny, nz, bx, by, bz, ux, uy, uz,
+                                                                                     Rs, octant);
+    k_newell_far<<<(unsigned)((4 * n + NT - 1) / NT), NT, 0, s>>>(nx, ny, nz, ux, uy, uz, Rs, octant);
     return hipGetLastError();
 }
 
