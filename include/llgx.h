@@ -224,9 +224,11 @@ llgx_status llgx_run(llgx_handle h, const llgx_stepper* s, double t_end, double 
  * summed milliseconds and launch counts per kernel kind since the last read,
  * and resets them. */
 #define LLGX_K_XFWD 0    /* stage combination + forward real-to-complex x pass */
-#define LLGX_K_YFWD 1    /* forward y pass                                    */
-#define LLGX_K_ZMUL 2    /* z forward, k-space tensor product, z inverse      */
-#define LLGX_K_YINV 3    /* inverse y pass                                    */
+#define LLGX_K_YFWD 1    /* forward y pass (not on thin meshes, see ZMUL)     */
+#define LLGX_K_ZMUL 2    /* z forward, k-space tensor product, z inverse; on
+                            thin meshes (nz <= 4) with both y passes in the
+                            same kernel                                      */
+#define LLGX_K_YINV 3    /* inverse y pass (not on thin meshes, see ZMUL)     */
 #define LLGX_K_XINV 4    /* inverse x pass fused with H_eff and the LLG RHS   */
 #define LLGX_K_COMBINE 5 /* stage input M_k = M0 + h sum b F (Eq. 4)          */
 #define LLGX_K_EXTRAP 6  /* Eq. (6) sub-step field + H_eff + LLG RHS          */

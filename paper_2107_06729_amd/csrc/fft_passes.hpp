@@ -102,11 +102,11 @@ struct XfwdShared<T, 0, ROWS> {
 };
 
 // rows row0 .. row0 + ROWS - 1 (one workgroup)
-template <typename T, typename S, int LX, int ROWS, bool HALF, bool STATIC_NF = false>
+template <typename T, typename S, int LX, int ROWS, bool HALF, bool STATIC_NF = false, bool BLK = false>
 __device__ __forceinline__ void xfwd_tile(const Combo<T>& in, T* __restrict__ mk_out, int nin, long nrows,
                                           typename Spec<T, S>::elem* __restrict__ spec, int SX,
                                           const cx<T>* __restrict__ twL, const cx<T>* __restrict__ twP, T fscale,
-                                          long row0, XfwdShared<T, LX, ROWS>& sh) {
+                                          long row0, XfwdShared<T, LX, ROWS>& sh, long blk_stride = 0) {
     using C = cx<T>;
     if constexpr (LX == 0) {
         for (int r = threadIdx.x; r < ROWS; r += NT) {
@@ -226,22 +226,24 @@ __device__ __forceinline__ void xfwd_tile(const Combo<T>& in, T* __restrict__ mk
             const C* rb = buf + r * F::RS;
             const C zk = rb[F::P(k)];
             const C zc = cconj(rb[F::P((LX - k) & (LX - 1))]);
-            const C E{(zk.x + zc.x) * T(0.5), (zk.y + zc.y) * T(0.5)};
-            const C O{(zk.y - zc.y) * T(0.5), (zc.x - zk.x) * T(0.5)};  // -i (zk - zc)/2
-            typename Spec<T, S>::elem* out = spec + g * SX;
-            out[k] = Spec<T, S>::put(cadd(E, cmul(O, twp[k])));
-            if (k == 0) out[LX] = Spec<T, S>::put(cadd(E, cmul(O, twp[LX])));
+            const C ev{(zk.x + zc.x) * T(0.5), (zk.y + zc.y) * T(0.5)};
+            const C od{(zk.y - zc.y) * T(0.5), (zc.x - zk.x) * T(0.5)};  // -i (zk - zc)/2
+            using E = typename Spec<T, S>::elem;
+            const SpecRow<BLK, E> out{spec + g * (BLK ? SpecBlock<E>::KB : SX), blk_stride};
+            out[k] = Spec<T, S>::put(cadd(ev, cmul(od, twp[k])));
+            if (k == 0) out[LX] = Spec<T, S>::put(cadd(ev, cmul(od, twp[LX])));
         }
     }
 }
 
-template <typename T, typename S, int LX, int ROWS, bool HALF>
+template <typename T, typename S, int LX, int ROWS, bool HALF, bool BLK>
 __global__ __launch_bounds__(NT) void k_xfwd(Combo<T> in, T* __restrict__ mk_out, int nin, long nrows,
-                                             typename Spec<T, S>::elem* __restrict__ spec, int SX,
+                                             typename Spec<T, S>::elem* __restrict__ spec, int SX, long blk_stride,
                                              const cx<T>* __restrict__ twL, const cx<T>* __restrict__ twP,
                                              T fscale) {
     __shared__ XfwdShared<T, LX, ROWS> sh;
-    xfwd_tile<T, S, LX, ROWS, HALF>(in, mk_out, nin, nrows, spec, SX, twL, twP, fscale, (long)blockIdx.x * ROWS, sh);
+    xfwd_tile<T, S, LX, ROWS, HALF, false, BLK>(in, mk_out, nin, nrows, spec, SX, twL, twP, fscale,
+                                                (long)blockIdx.x * ROWS, sh, blk_stride);
 }
 
 // ------------------------------------------------------------------------
@@ -258,11 +260,11 @@ struct XinvShared {
 };
 
 // row block bx of gx (the row blocks of one sample) of sample b
-template <typename T, typename S, int LX, int ROWS, int MODE>
+template <typename T, typename S, int LX, int ROWS, int MODE, bool BLK = false>
 __device__ __forceinline__ void xinv_tile(const typename Spec<T, S>::elem* __restrict__ spec, int SX,
                                           const T* __restrict__ M, const Phys<T>& ph, const XinvOut& out,
                                           const cx<T>* __restrict__ twL, const cx<T>* __restrict__ twP, T hscale,
-                                          int bx, int gx, int b, XinvShared<T, LX, ROWS>& sh) {
+                                          int bx, int gx, int b, XinvShared<T, LX, ROWS>& sh, long blk_stride = 0) {
     using C = cx<T>;
     constexpr int LXE = LX > 0 ? LX : 2;
     // only x < nx <= LX is kept: packed outputs z[j] with j < LX/2
@@ -283,7 +285,7 @@ __device__ __forceinline__ void xinv_tile(const typename Spec<T, S>::elem* __res
         y0 = yg * ROWS;
         row0 = (long)plane * ph.ny + y0;
     }
-    spec += (long)b * 3 * nrow * SX;
+    spec += (long)b * 3 * nrow * (BLK ? SpecBlock<typename Spec<T, S>::elem>::KB : SX);
     if (M) M += (long)b * 3 * N;
     const long vo = (long)b * 3 * N;
     if constexpr (LX == 0) {
@@ -314,8 +316,10 @@ __device__ __forceinline__ void xinv_tile(const typename Spec<T, S>::elem* __res
                 wk[m][q] = twP[k];
                 if (F::live0(u) && g < nrow) {
                     // (c nrow + g) < 3 ny nz <= 3 * 2^19 and SX <= 1040: exact in 32 bits
-                    const typename Spec<T, S>::elem* row =
-                        spec + __umul24((unsigned)(c * (int)nrow + (int)g), (unsigned)SX);
+                    using E = const typename Spec<T, S>::elem;
+                    const SpecRow<BLK, E> row{spec + __umul24((unsigned)(c * (int)nrow + (int)g),
+                                                              (unsigned)(BLK ? SpecBlock<E>::KB : SX)),
+                                              blk_stride};
                     xa[m][q] = Spec<T, S>::get(row[k]);
                     xb[m][q] = Spec<T, S>::get(row[LX - k]);
                 }
@@ -392,13 +396,14 @@ __device__ __forceinline__ void xinv_tile(const typename Spec<T, S>::elem* __res
     }
 }
 
-template <typename T, typename S, int LX, int ROWS, int MODE>
+template <typename T, typename S, int LX, int ROWS, int MODE, bool BLK>
 __global__ __launch_bounds__(NT) void k_xinv(const typename Spec<T, S>::elem* __restrict__ spec, int SX,
-                                             const T* __restrict__ M, Phys<T> ph, XinvOut out,
+                                             long blk_stride, const T* __restrict__ M, Phys<T> ph, XinvOut out,
                                              const cx<T>* __restrict__ twL, const cx<T>* __restrict__ twP,
                                              T hscale) {
     __shared__ XinvShared<T, LX, ROWS> sh;
-    xinv_tile<T, S, LX, ROWS, MODE>(spec, SX, M, ph, out, twL, twP, hscale, blockIdx.x, gridDim.x, blockIdx.y, sh);
+    xinv_tile<T, S, LX, ROWS, MODE, BLK>(spec, SX, M, ph, out, twL, twP, hscale, blockIdx.x, gridDim.x, blockIdx.y, sh,
+                                         blk_stride);
 }
 
 // ------------------------------------------------------------------------

@@ -116,12 +116,64 @@ struct RowFFT {
         }
     }
 
+    // stages between the first and the last (a barrier before, one at the end)
+    static __device__ __forceinline__ void middle(C* buf, const C* __restrict__ tw) {
+        if constexpr (NSTAGE > 2) mid_from<R0>(buf, tw);
+    }
+
+    // stage 0 from LDS (data in natural order, a barrier before); ends with a barrier
+    static __device__ __forceinline__ void first_in_lds(C* buf) {
+        C x[U0][R0];
+#pragma unroll
+        for (int m = 0; m < U0; ++m) {
+            const int u = threadIdx.x + m * NT;
+            if (live0(u)) {
+                int row, j;
+                unit<R0>(u, row, j);
+                const C* rb = buf + row * RS;
+#pragma unroll
+                for (int q = 0; q < R0; ++q) x[m][q] = rb[P(j + q * (L / R0))];
+            }
+        }
+        __syncthreads();
+        first_to_lds(x, buf);
+        __syncthreads();
+    }
+
+    // outputs x[8] of the last stage (elements j + r L/8) of one unit
+    static __device__ __forceinline__ void last_regs(const C* rb, const C* __restrict__ tw, int j, C (&x)[8]) {
+        constexpr int NS = L / 8;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const C a = rb[P(j + r * NS)];
+            const C w = tw[r * j];
+            x[r] = r == 0 ? a : (INV ? cmulc(a, w) : cmul(a, w));
+        }
+        dft_r<8, INV>(x);
+    }
+
+    // last stage, each kept output handed to f(row, element, value); NSTAGE >= 2
+    template <typename Fn>
+    static __device__ __forceinline__ void last_each(const C* buf, const C* __restrict__ tw, const Fn& f) {
+#pragma unroll
+        for (int m = 0; m < U8; ++m) {
+            const int u = threadIdx.x + m * NT;
+            if (NU8 % NT == 0 || u < NU8) {
+                int row, j;
+                unit<8>(u, row, j);
+                C x[8];
+                last_regs(buf + row * RS, tw, j, x);
+#pragma unroll
+                for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) f(row, j + r * (L / 8), x[r]);
+            }
+        }
+    }
+
     // every stage after the first; callers put a barrier after first_to_lds,
     // and this ends with one
     static __device__ __forceinline__ void rest(C* buf, const C* __restrict__ tw) {
         if constexpr (NSTAGE > 1) {
-            if constexpr (NSTAGE > 2) mid_from<R0>(buf, tw);
-            constexpr int NS = L / 8;
+            middle(buf, tw);
 #pragma unroll
             for (int m = 0; m < U8; ++m) {
                 const int u = threadIdx.x + m * NT;
@@ -130,15 +182,9 @@ struct RowFFT {
                     unit<8>(u, row, j);
                     C* rb = buf + row * RS;
                     C x[8];
+                    last_regs(rb, tw, j, x);
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const C a = rb[P(j + r * NS)];
-                        const C w = tw[r * j];
-                        x[r] = r == 0 ? a : (INV ? cmulc(a, w) : cmul(a, w));
-                    }
-                    dft_r<8, INV>(x);
-#pragma unroll
-                    for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) rb[P(j + r * NS)] = x[r];
+                    for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) rb[P(j + r * (L / 8))] = x[r];
                 }
             }
             __syncthreads();

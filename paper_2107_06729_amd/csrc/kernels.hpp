@@ -125,9 +125,10 @@ struct XinvOut {
 using SpecPtr = void*;
 template <typename T, typename S>
 hipError_t launch_xfwd(hipStream_t s, int LX, const Combo<T>& in, T* mk_out, int nin, long nrows, SpecPtr spec,
-                       int SX, const cx<T>* twL, const cx<T>* twP, T fscale, int variant);
+                       int SX, long blk_stride, const cx<T>* twL, const cx<T>* twP, T fscale, int variant);
 template <typename T, typename S>
-hipError_t launch_xinv(hipStream_t s, int LX, int mode, SpecPtr spec, int SX, const T* M, const Phys<T>& ph,
+hipError_t launch_xinv(hipStream_t s, int LX, int mode, SpecPtr spec, int SX, long blk_stride, const T* M,
+                       const Phys<T>& ph,
                        const XinvOut& out, const cx<T>* twL, const cx<T>* twP, T hscale, int variant);
 template <typename T, typename S>
 hipError_t launch_colfft(hipStream_t s, int L, bool inv, SpecPtr src, long s_cs, long s_os, long s_is, int n_in,
@@ -136,13 +137,22 @@ hipError_t launch_colfft(hipStream_t s, int L, bool inv, SpecPtr src, long s_cs,
 template <typename T, typename S>
 hipError_t launch_zmul(hipStream_t s, int LZ, SpecPtr buf, int SX, int Kx, int nz, int nyrows, int Py, int Pz,
                        const T* kfold, int Kyf, int Kzf, const cx<T>* tw, int nb, int variant);
+// Fused y/z pass of thin meshes (pass_yzy.hip): spectrum A blocked by 32
+// bytes of kx (SpecBlock), blk_stride elements apart (0 in the x passes above:
+// plain rows of SX); kcol is the folded kernel as [kx][kz][component][KYS].
+template <typename T, typename S>
+hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int Kx, int ny, int nz, int nb,
+                      const T* kcol, int KYS, const cx<T>* tw, T yscale, int variant);
+// whether the fused pass takes a mesh of nz cells padded to LY along y
+template <typename T>
+bool yzy_ok(int LY, int nz);
 hipError_t launch_newell_octant(hipStream_t s, int nx, int ny, int nz, double dx, double dy, double dz,
                                 double* octant);
 hipError_t launch_scatter_tensor(hipStream_t s, const double* octant, int comp, int nx, int ny, int nz,
                                  int Px, int Py, int Pz, double* real);
 template <typename T>
 hipError_t launch_fold(hipStream_t s, const cx<double>* spec, int SX, int Kx, int Py, int Pz, int Kyf, int Kzf,
-                       double scale, int comp, T* kfold, double* imag_max_parts, int nparts);
+                       double scale, int comp, T* kfold, T* kcol, int KYS, double* imag_max_parts, int nparts);
 
 // Folded k-space kernel layout: blocks of KB = 16 / sizeof(T) adjacent kx,
 // each block holding all (kz, component) values of one ky, so the z pass

@@ -17,6 +17,7 @@
 
 #include "batch.hpp"
 #include "kernels.hpp"
+#include "spec_store.hpp"
 #include "llgx.h"
 #include "tableaux.hpp"
 
@@ -77,9 +78,12 @@ struct Ctx {
     int var[5] = {0, 0, 0, 0, 0};  // launch variant per FFT pass (LLGX_K_XFWD .. LLGX_K_XINV)
     void* hab = nullptr;        // applied field of each sample [nb][3] (device, working precision)
     int Px = 1, Py = 1, Pz = 1, LX = 0, Kx = 1, SX = 16, Kyf = 1, Kzf = 1;
+    bool thin = false;          // y, z, y passes as one kernel on blocked spectra
+    int KYS = 1;                // row stride of kcol
 
     // device workspace
     void* kfold = nullptr;
+    void* kcol = nullptr;       // thin meshes: the kernel as the fused y/z pass reads it
     void* specA = nullptr;
     void* specB = nullptr;
     std::map<int, void*> tw_work;  // twiddle tables in the working precision
@@ -349,8 +353,12 @@ static void record_pass(Ctx* c, int kind, const EvalArgs<T>& a, void* A, void* B
     }
 }
 
+// thin meshes take the fused y/z pass (as LLGX_K_ZMUL) except in job-table
+// launches, which keep the separate passes of all groups
+static bool fused_yz(const Ctx* c) { return c->thin && !c->rec; }
+
 static bool pass_exists(const Ctx* c, int kind) {
-    return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && c->Py == 1);
+    return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && (c->Py == 1 || fused_yz(c)));
 }
 
 // launch one pass (kind LLGX_K_XFWD .. LLGX_K_XINV) with the handle's variant
@@ -370,11 +378,13 @@ static llgx_status run_pass(Ctx* c, int kind, const EvalArgs<T>& a) {
             c->rec_unsupported = true;
         return LLGX_OK;
     }
+    // blocked spectrum A of the fused pass: elements from one kx block to the next
+    const long blk = fused_yz(c) ? 3L * c->ny * c->nz * c->nb * SpecBlock<typename Spec<T, S>::elem>::KB : 0;
     switch (kind) {
         case LLGX_K_XFWD: {
             const T fscale = native ? T(1) : (T)(1.0 / (c->p.Ms * c->Px));
-            HIPCHK(c, (launch_xfwd<T, S>(s, c->LX, a.in, a.mk_out, c->nx, 3L * c->ny * c->nz * c->nb, A, c->SX, twL,
-                                         twP, fscale, c->var[kind])));
+            HIPCHK(c, (launch_xfwd<T, S>(s, c->LX, a.in, a.mk_out, c->nx, 3L * c->ny * c->nz * c->nb, A, c->SX, blk,
+                                         twL, twP, fscale, c->var[kind])));
             break;
         }
         case LLGX_K_YFWD: {
@@ -385,6 +395,12 @@ static llgx_status run_pass(Ctx* c, int kind, const EvalArgs<T>& a) {
             break;
         }
         case LLGX_K_ZMUL: {
+            if (fused_yz(c)) {
+                const T yscale = native ? T(1) : (T)(1.0 / c->Py);
+                HIPCHK(c, (launch_yzy<T, S>(s, c->Py, A, blk, c->Kx, c->ny, c->nz, c->nb, (const T*)c->kcol, c->KYS,
+                                            table<T>(c, c->Py, false), yscale, c->var[kind])));
+                break;
+            }
             void* work = c->Py > 1 ? B : A;
             const int nyrows = c->Py > 1 ? c->Py : c->ny;
             HIPCHK(c, (launch_zmul<T, S>(s, c->Pz, work, c->SX, c->Kx, c->nz, nyrows, c->Py, c->Pz,
@@ -399,8 +415,8 @@ static llgx_status run_pass(Ctx* c, int kind, const EvalArgs<T>& a) {
             break;
         case LLGX_K_XINV: {
             const T hscale = native ? T(1) : (T)c->p.Ms;
-            HIPCHK(c, (launch_xinv<T, S>(s, c->LX, a.mode, A, c->SX, a.Mrhs, phys<T>(c), a.out, twL, twP, hscale,
-                                         c->var[kind])));
+            HIPCHK(c, (launch_xinv<T, S>(s, c->LX, a.mode, A, c->SX, blk, a.Mrhs, phys<T>(c), a.out, twL, twP,
+                                         hscale, c->var[kind])));
             break;
         }
         default:
@@ -487,6 +503,14 @@ static llgx_status kernel_from_octant_or_real(Ctx* c, const std::vector<double>*
         }
         HIPCHK(c, hipMemsetAsync(c->kfold, 0, 6L * c->Kzf * c->Kyf * c->SX * sizeof(T), s));
     }
+    if (c->thin && !c->kcol) {
+        st = dalloc(c, &c->kcol, 6L * c->Kx * c->Kzf * c->KYS * sizeof(T));
+        if (st) {
+            (void)hipFree(real);
+            (void)hipFree(spec);
+            return st;
+        }
+    }
     for (int L : {c->LX, c->Px, c->Py, c->Pz}) {
         st = make_table<double>(c, c->tw_f64, L);
         if (st) return st;
@@ -517,7 +541,7 @@ static llgx_status kernel_from_octant_or_real(Ctx* c, const std::vector<double>*
         }
         cx<double>* sp = (cx<double>*)spec;
         HIPCHK(c, (launch_xfwd<double, double>(s, c->LX, plain<double>(real), nullptr, c->Px, (long)c->Pz * c->Py, sp,
-                                               c->SX, table<double>(c, c->LX, true), table<double>(c, c->Px, true),
+                                               c->SX, 0, table<double>(c, c->LX, true), table<double>(c, c->Px, true),
                                                1.0, 0)));
         if (c->Py > 1)
             HIPCHK(c, (launch_colfft<double, double>(s, c->Py, false, sp, 0, (long)c->Py * c->SX, c->SX, c->Py, sp, 0,
@@ -528,7 +552,7 @@ static llgx_status kernel_from_octant_or_real(Ctx* c, const std::vector<double>*
                                                      c->SX, (long)c->Py * c->SX, c->Pz, c->Kx, c->Py, 1,
                                                      table<double>(c, c->Pz, true), 1.0, 0)));
         HIPCHK(c, launch_fold<T>(s, sp, c->SX, c->Kx, c->Py, c->Pz, c->Kyf, c->Kzf, scale, comp, (T*)c->kfold,
-                                 c->parts, c->nparts));
+                                 (T*)c->kcol, c->KYS, c->parts, c->nparts));
     }
     HIPCHK(c, hipStreamSynchronize(s));
     (void)hipFree(real);
@@ -1281,7 +1305,7 @@ static void release(Ctx* c) {
     for (auto e : c->spare) (void)hipEventDestroy(e);
     for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     c->graphs.clear();
-    void* ptrs[] = {c->kfold, c->specA, c->specB,  c->M,      c->Mnew, c->Mk,
+    void* ptrs[] = {c->kfold, c->kcol, c->specA, c->specB,  c->M,      c->Mnew, c->Mk,
                     c->mk2_in_b ? nullptr : c->Mk2, c->parts, c->scal, c->octant, c->hab, c->empty_flag};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -1478,6 +1502,9 @@ static llgx_status create_ctx(const llgx_problem* p, int nb, const double* ha_li
     c->SX = (c->Kx + 15) / 16 * 16;
     c->Kyf = c->Py > 1 ? c->Py / 2 + 1 : 1;
     c->Kzf = c->Pz > 1 ? c->Pz / 2 + 1 : 1;
+    c->KYS = (c->Kyf + 7) / 8 * 8;
+    c->thin = c->LX > 0 && c->Py > 1 &&
+              (precision == LLGX_F32 ? yzy_ok<float>(c->Py, c->nz) : yzy_ok<double>(c->Py, c->nz));
     const size_t cbytes = spectral == LLGX_SPEC_NATIVE ? 2 * c->tsz : 4;  // bytes per stored complex value
     const size_t vbytes = 3 * (size_t)c->ncell * nb * c->tsz;
     llgx_status st = LLGX_OK;

@@ -223,11 +223,12 @@ __global__ void k_scatter_tensor(const double* __restrict__ oct, int comp, int n
 }
 
 // real part of one component's spectrum [Pz][Py][SX] -> folded kernel
-// [comp][Kzf][Kyf][SX] times scale; per-block max |Im| for the realness check
+// (kernel_index) and, for the fused pass of thin meshes (kcol given), its
+// [kx][kz][comp][KYS] form, times scale; per-block max |Im| for the realness check
 template <typename T>
 __global__ __launch_bounds__(NT) void k_fold(const cx<double>* __restrict__ spec, int SX, int Kx, int Py, int Kyf,
                                              int Kzf, double scale, int comp, T* __restrict__ kfold,
-                                             double* __restrict__ parts) {
+                                             T* __restrict__ kcol, int KYS, double* __restrict__ parts) {
     __shared__ double red[NT];
     const long n = (long)Kzf * Kyf * Kx;
     double mx = 0.0;
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(NT) void k_fold(const cx<double>* __restrict__ spec
         const int kyf = (int)(r % Kyf), kzf = (int)(r / Kyf);
         const cx<double> v = spec[((long)kzf * Py + kyf) * SX + kx];
         kfold[kernel_index<T>(kyf, kx, kzf, comp, SX, Kzf)] = (T)(v.x * scale);
+        if (kcol) kcol[(((long)kx * Kzf + kzf) * 6 + comp) * KYS + kyf] = (T)(v.x * scale);
         mx = fmax(mx, fabs(v.y * scale));
     }
     red[threadIdx.x] = mx;
@@ -276,15 +278,15 @@ hipError_t launch_scatter_tensor(hipStream_t s, const double* octant, int comp, 
 
 template <typename T>
 hipError_t launch_fold(hipStream_t s, const cx<double>* spec, int SX, int Kx, int Py, int Pz, int Kyf, int Kzf,
-                       double scale, int comp, T* kfold, double* parts, int nparts) {
+                       double scale, int comp, T* kfold, T* kcol, int KYS, double* parts, int nparts) {
     (void)Pz;
-    k_fold<T><<<(unsigned)nparts, NT, 0, s>>>(spec, SX, Kx, Py, Kyf, Kzf, scale, comp, kfold, parts);
+    k_fold<T><<<(unsigned)nparts, NT, 0, s>>>(spec, SX, Kx, Py, Kyf, Kzf, scale, comp, kfold, kcol, KYS, parts);
     return hipGetLastError();
 }
 
 template hipError_t launch_fold<float>(hipStream_t, const cx<double>*, int, int, int, int, int, int, double, int,
-                                       float*, double*, int);
+                                       float*, float*, int, double*, int);
 template hipError_t launch_fold<double>(hipStream_t, const cx<double>*, int, int, int, int, int, int, double, int,
-                                        double*, double*, int);
+                                        double*, double*, int, double*, int);
 
 }  // namespace llgx

@@ -1,0 +1,82 @@
+// Launcher of the fused y/z pass of thin meshes (Eq. (2)).
+#include "pass_yzy.hpp"
+
+namespace llgx {
+
+// Threads of a tile.  Variant 0 gives every stage whole rounds: 3 nz LY/8
+// radix-8 butterflies against LY product units.  Above 512 threads a second
+// tile no longer fits beside the first (registers), and the last columns of
+// an odd Kx run alone: 256x256x4 FP32 17.7 us with 768 threads, 14.3 with 512.
+// Variants 1 and 2 (half of LY, LY) are the faster ones on some shapes
+// (512x512x2 FP64 57.0 against 57.3, 1000x100x4 FP32 17.0 against 20.0).
+constexpr int yzy_nth(int LY, int nz, int v) {
+    const int n = v == 1 ? LY / 2 : v == 2 ? LY : nz == 1 ? LY / 2 : nz == 2 ? LY : LY * 3 * nz / 8;
+    const int r = (n + 63) / 64 * 64;
+    return r < 64 ? 64 : r > 512 ? 512 : r;
+}
+
+// The fused pass takes every thin mesh whose one-column tile fits a CU's LDS
+// with room for the tile's launch beside it.  Microseconds of the y, z and y
+// passes with their default tiles against this one, back to back:
+//   60x60x1 FP32 10.1 / 4.2, 256x64x1 FP32 9.9 / 4.3, 32x32x2 FP64 8.7 / 3.9,
+//   128x128x4 FP32 12.6 / 6.6, 256x256x4 FP32 23.1 / 14.3 and FP64 35.6 / 30.5,
+//   512x512x1 FP32 28.5 / 13.4, 300x512x4 FP32 69 / 59, 1000x1000x2 FP32 178 / 99,
+//   7x1000x2 FP32 26 / 18.
+// On the largest tiles (110 KB: one workgroup a CU) the separate passes come
+// level once autotuned (300x512x4: 58), so larger ones are not taken.
+template <typename T>
+bool yzy_ok(int LY, int nz) {
+    return LY >= 2 && LY <= MAX_LEN && nz >= 1 && nz <= YZY_MAX_NZ && yzy_lds<T>(LY, nz, 1) <= YZY_LDS_MAX;
+}
+template bool yzy_ok<float>(int, int);
+template bool yzy_ok<double>(int, int);
+
+template <typename T, typename S>
+hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int Kx, int ny, int nz, int nb,
+                      const T* kcol, int KYS, const cx<T>* tw, T yscale, int variant) {
+    using E = typename Spec<T, S>::elem;
+    E* sp = (E*)spec;
+    if (variant < 0 || variant >= NVAR_ZMUL || 2 * ny > LY + 1 || KYS < LY / 2 + 1) return hipErrorInvalidValue;
+    if ((long)3 * nz * ny * SpecBlock<E>::KB >= (1L << 31)) return hipErrorInvalidValue;
+#define YZ_L(LL, NZ, V)                                                                                       \
+    k_yzy<T, S, LL, NZ, 1, yzy_nth(LL, NZ, V)><<<dim3((unsigned)Kx, (unsigned)nb), yzy_nth(LL, NZ, V), 0, s>>>( \
+        sp, blk_stride, Kx, ny, kcol, KYS, tw, yscale)
+#define YZ_N(LL, NZ)                                          \
+    case NZ:                                                  \
+        if constexpr (yzy_lds<T>(LL, NZ, 1) <= YZY_LDS_MAX) { \
+            if (variant == 0)                                 \
+                YZ_L(LL, NZ, 0);                              \
+            else if (variant == 1)                            \
+                YZ_L(LL, NZ, 1);                              \
+            else                                              \
+                YZ_L(LL, NZ, 2);                              \
+            return hipGetLastError();                         \
+        }                                                     \
+        return hipErrorInvalidValue;
+#define YZ(LL)                                             \
+    case LL:                                               \
+        switch (nz) {                                      \
+            YZ_N(LL, 1) YZ_N(LL, 2) YZ_N(LL, 3) YZ_N(LL, 4) \
+            default:                                       \
+                return hipErrorInvalidValue;               \
+        }
+    switch (LY) {
+        YZ(2) YZ(4) YZ(8) YZ(16) YZ(32) YZ(64) YZ(128) YZ(256) YZ(512) YZ(1024) YZ(2048)
+        default:
+            return hipErrorInvalidValue;
+    }
+#undef YZ
+#undef YZ_N
+#undef YZ_L
+}
+
+#define INST_TS(T, S)                                                                                          \
+    template hipError_t launch_yzy<T, S>(hipStream_t, int, SpecPtr, long, int, int, int, int, const T*, int, \
+                                         const cx<T>*, T, int);
+INST_TS(float, float)
+INST_TS(float, _Float16)
+INST_TS(float, __bf16)
+INST_TS(double, double)
+#undef INST_TS
+
+}  // namespace llgx

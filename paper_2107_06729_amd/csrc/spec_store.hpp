@@ -35,6 +35,25 @@ template <> struct Spec<float, __bf16> {
     static __device__ __forceinline__ elem put(const float2& v) { return elem{(__bf16)v.x, (__bf16)v.y}; }
 };
 
+// Columns kx of one 32-byte block of a blocked spectrum (thin meshes):
+// [kx / KB][row][kx % KB]
+template <typename E>
+struct SpecBlock {
+    static constexpr int KB = 32 / (int)sizeof(E);
+};
+
+// One row of a spectrum: contiguous (BLK false: base at the row's start), or
+// in blocks of KB columns a blk_stride apart (BLK: base at the first block)
+template <bool BLK, typename E>
+struct SpecRow {
+    E* p;
+    long bs;
+    __device__ __forceinline__ E& operator[](int k) const {
+        if constexpr (BLK) return p[(k / SpecBlock<E>::KB) * bs + k % SpecBlock<E>::KB];
+        else return p[k];
+    }
+};
+
 template <int BYTES> struct Raw;
 template <> struct Raw<4> { using type = unsigned int; };
 template <> struct Raw<8> { using type = uint2; };
