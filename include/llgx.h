@@ -182,7 +182,8 @@ llgx_status llgx_rhs(llgx_handle h, const void* M_dev, void* F_dev);
  * frees nothing, issues no hipMemset, and enqueues kernels only.
  * The mesh must fit: 256 + round_up(SA, 256) + SB bytes, with
  *   SA = 3 nz ny SX c, SB = 3 nz Py SX c (0 when ny = 1),
- *   Px/Py = next power of two >= 2 nx - 1 / 2 ny - 1 (1 for nx/ny = 1),
+ *   Px/Py = next power of two >= 2 nx - 1 / 2 ny - 1 (1 for nx/ny = 1; an
+ *   upper bound of the lengths the passes pad to),
  *   SX = round_up(Px/2 + 1, 16), c = bytes per stored complex value
  *   (16 FP64, 8 FP32, 4 with 16-bit spectra); e.g. FP32 256x256x16 needs
  *   80.2 MB.  A larger mesh gives LLGX_E_ARG and enqueues nothing.

@@ -14,7 +14,10 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libllgx.so")
-SOURCES = ["pass_x.hip", "pass_col.hip", "pass_z.hip", "pass_yzy.hip", "newell.hip", "llg.hip", "batch.hip", "llgx_api.hip"]
+# (source, LLGX_INST): the FFT passes are built once per working precision and
+# spectra storage (0 FP32, 1 FP16, 2 BF16, 3 FP64), the longest objects first
+SOURCES = [(s, k) for s in ("pass_yzy.hip", "pass_x.hip", "pass_z.hip", "pass_col.hip") for k in (3, 0, 1, 2)]
+SOURCES += [(s, None) for s in ("batch.hip", "llg.hip", "llgx_api.hip", "newell.hip")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -60,10 +63,11 @@ def build(verbose=False, jobs=None):
     jobs = jobs or min(len(SOURCES), os.cpu_count() or 1)
     objs = []
     cmds = []
-    for s in SOURCES:
-        o = os.path.join(BUILD, os.path.splitext(s)[0] + ".o")
+    for s, k in SOURCES:
+        o = os.path.join(BUILD, os.path.splitext(s)[0] + ("" if k is None else f"_{k}") + ".o")
         objs.append(o)
-        cmds.append([HIPCC] + CFLAGS + ["-c", os.path.join(CSRC, s), "-o", o])
+        inst = [] if k is None else [f"-DLLGX_INST={k}"]
+        cmds.append([HIPCC] + CFLAGS + inst + ["-c", os.path.join(CSRC, s), "-o", o])
     with ThreadPoolExecutor(jobs) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
     tmp = LIB + ".tmp"

@@ -412,7 +412,8 @@ static const void* xfwd_fn(int LX) {
         case 0: return (const void*)kb_xfwd<T, 0, 256, false>;
 #define C_(L) \
     case L: return (const void*)kb_xfwd<T, L, bx_rows<T>(L), true>;
-        C_(2) C_(4) C_(8) C_(16) C_(32) C_(64) C_(128) C_(256) C_(512)
+        C_(2) C_(4) C_(8) C_(16) C_(24) C_(32) C_(40) C_(48) C_(64) C_(80) C_(96) C_(128) C_(160) C_(192) C_(256) C_(320)
+        C_(384) C_(512)
 #undef C_
     }
     return nullptr;
@@ -422,7 +423,8 @@ static const void* col_fn(int L) {
     switch (L) {
 #define C_(LL) \
     case LL: return (const void*)kb_col<T, LL, INV, bc_tile<T>(LL)>;
-        C_(2) C_(4) C_(8) C_(16) C_(32) C_(64) C_(128) C_(256) C_(512)
+        C_(2) C_(4) C_(8) C_(16) C_(24) C_(32) C_(40) C_(48) C_(64) C_(80) C_(96) C_(128) C_(160) C_(192) C_(256) C_(320)
+        C_(384) C_(512)
 #undef C_
     }
     return nullptr;
@@ -432,7 +434,7 @@ static const void* zmul_fn(int LZ) {
     switch (LZ) {
 #define C_(L) \
     case L: return (const void*)kb_zmul<T, L, bz_tile<T>(L)>;
-        C_(1) C_(4) C_(8) C_(16) C_(32) C_(64)
+        C_(1) C_(4) C_(8) C_(16) C_(24) C_(32) C_(40) C_(48) C_(64)
 #undef C_
     }
     return nullptr;
@@ -442,7 +444,8 @@ static const void* xinv_fn(int LX) {
     switch (LX) {
 #define C_(L) \
     case L: return (const void*)kb_xinv<T, L, bi_rows<T>(L)>;
-        C_(0) C_(2) C_(4) C_(8) C_(16) C_(32) C_(64) C_(128) C_(256) C_(512)
+        C_(0) C_(2) C_(4) C_(8) C_(16) C_(24) C_(32) C_(40) C_(48) C_(64) C_(80) C_(96) C_(128) C_(160) C_(192) C_(256)
+        C_(320) C_(384) C_(512)
 #undef C_
     }
     return nullptr;

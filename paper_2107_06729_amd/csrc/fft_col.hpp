@@ -4,7 +4,7 @@
 // Group g of the tile is TK adjacent columns starting at a global address
 // given by a Bases functor; element (row i, group g, column c) lives in LDS at
 // buf[i * W + g * TK + c], W = NG * TK.  The stage schedule is the one of
-// fft_lds.hpp (a radix-R0 stage, R0 = 2, 4 or 8, then radix-8 stages).  Here
+// fft_lds.hpp (a radix-R0 stage, then radix-8 stages).  Here
 //   * stage 0 (span 1, no twiddles) takes its inputs x[j + r L/R0] straight
 //     from global rows (rows >= n_in are the zero padding and are not read)
 //     and writes its outputs to LDS rows j R0 + r;
@@ -12,7 +12,7 @@
 //     the same rows and go either straight to global rows < n_out or back to
 //     LDS in place;
 //   * stages in between run LDS to LDS.
-// A transform of length L <= 8 is one stage, global to global.
+// A transform of length L = R0 (at most 8) is one stage, global to global.
 //
 // Work unit of every stage: one butterfly row j for one 16-byte storage pack
 // of PN adjacent columns of one group (PN = 2 FP32, 1 FP64, 4 for 16-bit
@@ -23,8 +23,8 @@
 // written.
 //
 // HALF_IN: the caller guarantees that input rows >= L/2 are zero (a zero
-// padded forward transform: n_in <= L/2), so stage 0 neither loads them nor
-// transforms them (its radix-R0 butterflies take R0/2 non-zero inputs).
+// padded forward transform: n_in <= L/2), so stage 0 does not load them (its radix-R0
+// butterflies take at most (R0 + 1)/2 non-zero inputs).
 // HALF_OUT: only output rows < L/2 are wanted (n_out <= L/2), so the last
 // stage forms only the first half of its radix-8 outputs.
 #pragma once
@@ -61,7 +61,7 @@ struct ColFFT {
     static constexpr int NP = TK / PN;  // packs per group row
     static constexpr int W = NG * TK;   // LDS row width (complex)
     static constexpr int R0 = first_radix(L);
-    static constexpr int NSTAGE = 1 + (ilog2(L) - ilog2(R0)) / 3;
+    static constexpr int NSTAGE = fft_stages(L);
     static constexpr int NU0 = (L / R0) * NG * NP, U0 = (NU0 + NT - 1) / NT;  // stage-0 units per tile / thread
     static constexpr int NU8 = (L / 8) * NG * NP, U8 = (NU8 + NT - 1) / NT;   // radix-8 stage units
     static constexpr int LDS_ELEMS = L * W;
@@ -180,7 +180,7 @@ struct ColFFT {
             const int u = threadIdx.x + m * NT;
             if (NU8 % NT == 0 || u < NU8) {
                 const Unit t = unit(u);
-                const int k = t.j & (NS - 1);
+                const int k = t.j % NS;
                 const C* col = buf + t.g * TK + t.p * PN;
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
@@ -201,7 +201,7 @@ struct ColFFT {
             const int u = threadIdx.x + m * NT;
             if (NU8 % NT == 0 || u < NU8) {
                 const Unit t = unit(u);
-                const int k = t.j & (NS - 1);
+                const int k = t.j % NS;
                 const int base = (t.j / NS) * NS * 8 + k;
                 C* col = buf + t.g * TK + t.p * PN;
 #pragma unroll

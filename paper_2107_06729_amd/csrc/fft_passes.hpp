@@ -41,15 +41,18 @@ constexpr int col_tile(int L, int v) {
 }
 template <typename T>
 constexpr int zmul_tile(int L, int v) {
-    const int t = sizeof(T) == 4 ? (L <= 64 ? 16 : L == 128 ? 8 : L == 256 ? 4 : 2)
-                                 : (L <= 64 ? 8 : L == 128 ? 4 : L == 256 ? 2 : 1);
+    const int t = sizeof(T) == 4 ? (L <= 64 ? 16 : L <= 128 ? 8 : L <= 256 ? 4 : 2)
+                                 : (L <= 64 ? 8 : L <= 128 ? 4 : L <= 256 ? 2 : 1);
     // variant 2 doubles the tile while its spectrum stays within 48 KiB of LDS
     const bool fits = (long)(L > 1 ? L : 1) * 6 * 2 * t * 2 * (long)sizeof(T) <= 48 * 1024;
     return v == 1 ? (t > 1 ? t / 2 : 1) : (v == 2 && fits) ? 2 * t : t;
 }
+// rows are a power of two: they divide more mesh heights (the y-slab order of
+// the x inverse needs that)
+constexpr int floor_pow2(int n) { return n < 2 ? 1 : 2 * floor_pow2(n / 2); }
 template <typename T>
 constexpr int xfwd_rows(int LX, int v) {
-    int r = (sizeof(T) == 4 ? 2048 : 1024) / (LX > 0 ? LX : 1);
+    int r = floor_pow2((sizeof(T) == 4 ? 2048 : 1024) / (LX > 0 ? LX : 1));
     r = r < 1 ? 1 : (r > 16 ? 16 : r);
     // variant 2 doubles the rows while the tile stays within 48 KiB of LDS
     const bool fits = 2L * r * (LX + 1) * 2 * (long)sizeof(T) <= 48 * 1024;
@@ -57,13 +60,11 @@ constexpr int xfwd_rows(int LX, int v) {
 }
 template <typename T>
 constexpr int xinv_rows(int LX, int v) {
-    int r = (sizeof(T) == 4 ? 1024 : 512) / (LX > 0 ? LX : 1);
+    int r = floor_pow2((sizeof(T) == 4 ? 1024 : 512) / (LX > 0 ? LX : 1));
     r = r < 1 ? 1 : (r > 8 ? 8 : r);
     const bool fits = 2L * 3 * r * (LX + 1) * 2 * (long)sizeof(T) <= 48 * 1024;
     return v == 1 ? (r > 1 ? r / 2 : 1) : (v == 2 && fits) ? 2 * r : r;
 }
-
-#define LLGX_POW2_CASES(M) M(2) M(4) M(8) M(16) M(32) M(64) M(128) M(256) M(512) M(1024) M(2048)
 
 // Eq. (4) terms: a loop over c.nf (kernel arguments, indexed in place), or
 // with STATIC_NF unrolled to MAX_F with static indices (arguments held in
@@ -165,7 +166,7 @@ __device__ __forceinline__ void xfwd_tile(const Combo<T>& in, T* __restrict__ mk
             }
             return w;
         };
-        constexpr int QN = HALF ? F::R0 / 2 : F::R0;  // inputs q >= QN lie in the zero half
+        constexpr int QN = HALF ? (F::R0 + 1) / 2 : F::R0;  // inputs q >= QN lie in the zero half
 #pragma unroll
         for (int m = 0; m < F::U0; ++m)
 #pragma unroll
@@ -220,12 +221,12 @@ __device__ __forceinline__ void xfwd_tile(const Combo<T>& in, T* __restrict__ mk
         // X[k] for k < LX; the lane of k = 0 also writes X[LX], which takes
         // the same z_0 (LX - k and k both wrap to 0)
         for (int e = threadIdx.x; e < ROWS * LX; e += NT) {
-            const int r = e / LX, k = e & (LX - 1);
+            const int r = e / LX, k = e - r * LX;
             const long g = row0 + r;
             if (g >= nrows) continue;
             const C* rb = buf + r * F::RS;
             const C zk = rb[F::P(k)];
-            const C zc = cconj(rb[F::P((LX - k) & (LX - 1))]);
+            const C zc = cconj(rb[F::P(k == 0 ? 0 : LX - k)]);
             const C ev{(zk.x + zc.x) * T(0.5), (zk.y + zc.y) * T(0.5)};
             const C od{(zk.y - zc.y) * T(0.5), (zc.x - zk.x) * T(0.5)};  // -i (zk - zc)/2
             using E = typename Spec<T, S>::elem;

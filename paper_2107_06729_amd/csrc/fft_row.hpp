@@ -3,7 +3,7 @@
 // NR rows of length L; element i of row r lives at buf[r * RS + P(i)] with
 // P(i) = i + i / 8: one padding element after every 8, so the stride-R0
 // writes of the first stage spread over the banks.  The stage
-// schedule is that of fft_lds.hpp (radix R0 = 2, 4 or 8, then radix 8).
+// schedule is that of fft_lds.hpp (radix R0, then radix 8).
 //
 // Work unit of every stage: one butterfly j of one row, j fastest, so
 // consecutive threads touch consecutive elements.  The first stage takes its
@@ -26,7 +26,7 @@ template <typename T, int L, bool INV, int NR, int NT, bool HALF_IN = false, boo
 struct RowFFT {
     using C = cx<T>;
     static constexpr int R0 = first_radix(L);
-    static constexpr int NSTAGE = 1 + (ilog2(L) - ilog2(R0)) / 3;
+    static constexpr int NSTAGE = fft_stages(L);
     static constexpr int RS = L + L / 8 + 1;  // padded row stride (complex)
     static constexpr int LDS_ELEMS = NR * RS;
     static constexpr int NU0 = NR * (L / R0), U0 = (NU0 + NT - 1) / NT;
@@ -61,7 +61,7 @@ struct RowFFT {
                 unit<R0>(u, row, j);
                 if constexpr (HALF_IN) {
 #pragma unroll
-                    for (int q = R0 / 2; q < R0; ++q) x[m][q] = C{T(0), T(0)};
+                    for (int q = (R0 + 1) / 2; q < R0; ++q) x[m][q] = C{T(0), T(0)};
                 }
                 dft_r<R0, INV>(x[m]);
                 C* rb = buf + row * RS;
@@ -80,7 +80,7 @@ struct RowFFT {
             if (NU8 % NT == 0 || u < NU8) {
                 int row, j;
                 unit<8>(u, row, j);
-                const int k = j & (NS - 1);
+                const int k = j % NS;
                 const C* rb = buf + row * RS;
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
@@ -98,7 +98,7 @@ struct RowFFT {
             if (NU8 % NT == 0 || u < NU8) {
                 int row, j;
                 unit<8>(u, row, j);
-                const int k = j & (NS - 1);
+                const int k = j % NS;
                 const int base = (j / NS) * NS * 8 + k;
                 C* rb = buf + row * RS;
 #pragma unroll

@@ -117,7 +117,7 @@ struct XinvOut {
 };
 
 // Host-side launchers of the FFT passes (pass_x.hip, pass_col.hip, pass_z.hip)
-// and of the tensor setup (newell.hip).  All lengths are powers of two.  Spectra
+// and of the tensor setup (newell.hip).  Lengths as listed in fft_lds.hpp.  Spectra
 // are passed untyped (SpecPtr) and stored as S: the working precision T, or
 // _Float16 / __bf16 pairs for T = float.  fscale, scale and hscale multiply
 // the x-pass input, the y-pass output and the final field (all 1 for storage

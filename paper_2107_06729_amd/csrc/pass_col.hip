@@ -49,7 +49,7 @@ hipError_t launch_colfft(hipStream_t s, int L, bool inv, SpecPtr src, long s_cs,
         break;                                          \
     }
     switch (L) {
-        LLGX_POW2_CASES(CF)
+        LLGX_FFT_LENGTHS(CF) LLGX_FFT_LENGTHS_LONG(CF)
         default:
             return hipErrorInvalidValue;
     }
@@ -62,10 +62,16 @@ hipError_t launch_colfft(hipStream_t s, int L, bool inv, SpecPtr src, long s_cs,
 #define INST_TS(T, S)                                                                                         \
     template hipError_t launch_colfft<T, S>(hipStream_t, int, bool, SpecPtr, long, long, long, int, SpecPtr, long, \
                                             long, long, int, int, int, int, const cx<T>*, T, int);
+// one object per working precision and storage (build_lib.py)
+#if LLGX_INST == 0
 INST_TS(float, float)
+#elif LLGX_INST == 1
 INST_TS(float, _Float16)
+#elif LLGX_INST == 2
 INST_TS(float, __bf16)
+#else
 INST_TS(double, double)
+#endif
 #undef INST_TS
 
 }  // namespace llgx

@@ -42,7 +42,7 @@ hipError_t launch_xfwd(hipStream_t s, int LX, const Combo<T>& in, T* mk_out, int
         case 0:
             XF_R(0, 256);
             break;
-        LLGX_POW2_CASES(XF)
+        LLGX_FFT_LENGTHS(XF)
         default:
             return hipErrorInvalidValue;
     }
@@ -96,7 +96,7 @@ hipError_t launch_xinv(hipStream_t s, int LX, int mode, SpecPtr spec, int SX, lo
             XI_MODE(0, R)
             break;
         }
-        LLGX_POW2_CASES(XI)
+        LLGX_FFT_LENGTHS(XI)
         default:
             return hipErrorInvalidValue;
     }
@@ -112,10 +112,16 @@ hipError_t launch_xinv(hipStream_t s, int LX, int mode, SpecPtr spec, int SX, lo
                                           const cx<T>*, const cx<T>*, T, int);                                   \
     template hipError_t launch_xinv<T, S>(hipStream_t, int, int, SpecPtr, int, long, const T*, const Phys<T>&,    \
                                           const XinvOut&, const cx<T>*, const cx<T>*, T, int);
+// one object per working precision and storage (build_lib.py)
+#if LLGX_INST == 0
 INST_TS(float, float)
+#elif LLGX_INST == 1
 INST_TS(float, _Float16)
+#elif LLGX_INST == 2
 INST_TS(float, __bf16)
+#else
 INST_TS(double, double)
+#endif
 #undef INST_TS
 
 }  // namespace llgx

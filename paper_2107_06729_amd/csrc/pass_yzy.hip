@@ -28,8 +28,11 @@ template <typename T>
 bool yzy_ok(int LY, int nz) {
     return LY >= 2 && LY <= MAX_LEN && nz >= 1 && nz <= YZY_MAX_NZ && yzy_lds<T>(LY, nz, 1) <= YZY_LDS_MAX;
 }
+#if LLGX_INST == 0
 template bool yzy_ok<float>(int, int);
+#elif LLGX_INST == 3
 template bool yzy_ok<double>(int, int);
+#endif
 
 template <typename T, typename S>
 hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int Kx, int ny, int nz, int nb,
@@ -61,7 +64,7 @@ hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int 
                 return hipErrorInvalidValue;               \
         }
     switch (LY) {
-        YZ(2) YZ(4) YZ(8) YZ(16) YZ(32) YZ(64) YZ(128) YZ(256) YZ(512) YZ(1024) YZ(2048)
+        LLGX_FFT_LENGTHS(YZ) LLGX_FFT_LENGTHS_LONG(YZ)
         default:
             return hipErrorInvalidValue;
     }
@@ -73,10 +76,16 @@ hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int 
 #define INST_TS(T, S)                                                                                          \
     template hipError_t launch_yzy<T, S>(hipStream_t, int, SpecPtr, long, int, int, int, int, const T*, int, \
                                          const cx<T>*, T, int);
+// one object per working precision and storage (build_lib.py)
+#if LLGX_INST == 0
 INST_TS(float, float)
+#elif LLGX_INST == 1
 INST_TS(float, _Float16)
+#elif LLGX_INST == 2
 INST_TS(float, __bf16)
+#else
 INST_TS(double, double)
+#endif
 #undef INST_TS
 
 }  // namespace llgx

@@ -35,7 +35,7 @@ hipError_t launch_zmul(hipStream_t s, int LZ, SpecPtr buf, int SX, int Kx, int n
         break;                                          \
     }
     switch (LZ) {
-        ZM(1) ZM(2) ZM(4) ZM(8) ZM(16) ZM(32) ZM(64) ZM(128) ZM(256) ZM(512) ZM(1024)
+        ZM(1) LLGX_FFT_LENGTHS(ZM)
         default:
             return hipErrorInvalidValue;
     }
@@ -47,10 +47,16 @@ hipError_t launch_zmul(hipStream_t s, int LZ, SpecPtr buf, int SX, int Kx, int n
 #define INST_TS(T, S)                                                                                         \
     template hipError_t launch_zmul<T, S>(hipStream_t, int, SpecPtr, int, int, int, int, int, int, const T*, int,  \
                                           int, const cx<T>*, int, int);
+// one object per working precision and storage (build_lib.py)
+#if LLGX_INST == 0
 INST_TS(float, float)
+#elif LLGX_INST == 1
 INST_TS(float, _Float16)
+#elif LLGX_INST == 2
 INST_TS(float, __bf16)
+#else
 INST_TS(double, double)
+#endif
 #undef INST_TS
 
 }  // namespace llgx
