@@ -313,6 +313,7 @@ __global__ __launch_bounds__(NT) void kb_xfwd(const BJobs<BXfwd<T>>* __restrict_
 
 template <typename T, int L, bool INV, int TK>
 __global__ __launch_bounds__(NT) void kb_col(const BJobs<BCol<T>>* __restrict__ J) {
+    static_assert(col_threads(L, TK) == NT, "launched with NT threads");
     __shared__ ColShared<T, T, L, TK> sh;
     BATCH_JOB(J)
     const BCol<T> a = job_args(&J->g[g]);
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(NT) void kb_col(const BJobs<BCol<T>>* __restrict__ 
 }
 
 template <typename T, int LZ, int TK>
-__global__ __launch_bounds__(NT) void kb_zmul(const BJobs<BZmul<T>>* __restrict__ J) {
+__global__ __launch_bounds__(zmul_threads<T>(LZ, TK)) void kb_zmul(const BJobs<BZmul<T>>* __restrict__ J) {
     __shared__ ZmulShared<T, LZ, TK> sh;
     BATCH_JOB(J)
     const BZmul<T> a = job_args(&J->g[g]);
@@ -467,12 +468,13 @@ static hipError_t finish(const void* f, BJobs<A>& J, std::vector<unsigned char>&
     blob.resize(out.offset + sizeof(BJobs<A>));
     std::memcpy(blob.data() + out.offset, &J, sizeof(BJobs<A>));
     out.fn = f;
+    out.threads = NT;
     return hipSuccess;
 }
 
 hipError_t enqueue_batch(const BatchLaunch& b, const void* table_dev, hipStream_t s) {
     void* args[] = {(void*)&table_dev};
-    return hipLaunchKernel(b.fn, dim3(b.grid), dim3(NT), args, 0, s);
+    return hipLaunchKernel(b.fn, dim3(b.grid), dim3(b.threads), args, 0, s);
 }
 
 template <typename T>
@@ -544,7 +546,10 @@ hipError_t prepare_batch(int kind, int nf, const std::vector<const void*>& args,
                 a.jobs = a.ntile * a.nq * a.nb;
             }
             const void* f = zmul_fn<T>(LZ);
-            return f ? finish<BZmul<T>>(f, J, blob, out) : hipErrorInvalidValue;
+            if (!f) return hipErrorInvalidValue;
+            const hipError_t e = finish<BZmul<T>>(f, J, blob, out);
+            out.threads = (unsigned)zmul_threads<T>(LZ, bz_tile<T>(LZ));
+            return e;
         }
         case BK_XINV: {
             BJobs<BXinv<T>> J{};

@@ -127,6 +127,7 @@ struct BJobs {
 struct BatchLaunch {
     int kind, nf;
     unsigned grid;   // workgroups: one per job and padding slot
+    unsigned threads;  // of a workgroup
     size_t offset;   // of the job table in the table buffer
     const void* fn;  // the kernel (its one argument: the job table)
 };

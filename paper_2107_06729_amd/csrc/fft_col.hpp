@@ -30,6 +30,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fft_lds.hpp"
 #include "spec_store.hpp"
 
@@ -42,26 +44,39 @@ struct Base1 {
     __device__ __forceinline__ E* operator()(int) const { return p; }
 };
 
-// Element offset j * gs of a unit's first transform row j < L/2, in one
-// 24-bit multiply.  Exact when gs < 2^24 and (L/2) gs < 2^32, which the
-// launchers check (rows along y: L <= 2048 at stride SX <= 1040; along z:
-// L <= 1024 at stride Py SX <= 2048 * 1040).  The unit's other rows add
-// uniform offsets.
+// Element offset j * gs of a row j < L/2, in one 24-bit multiply (a 64-bit
+// product costs eight times as much).  Exact when gs < 2^24 and L gs <
+// 2^32, which the launchers check (rows along y: L <= 2048 at stride SX <=
+// 1040; along z: L <= 1024 at stride Py SX <= 2048 * 1040).  Inputs: every row
+// that is read; outputs: a unit's first row, its others add uniform offsets.
 __device__ __forceinline__ unsigned row_off(int j, long gs) { return __umul24((unsigned)j, (unsigned)gs); }
-inline bool row_off_ok(int L, long gs) { return gs >= 0 && gs < (1L << 24) && (long)(L / 2) * gs < (1L << 32); }
+inline bool row_off_ok(int L, long gs) { return gs >= 0 && gs < (1L << 24) && (long)L * gs < (1L << 32); }
+
+// First radix of a column transform: 16 takes a stage less than 2 8 8 (8).  It
+// pays in FP32 in the z pass (NG = 6 groups) and at 1024 (y inverse of
+// 512x512x64 269 -> 256 us); in the
+// y pass of length 128 half the threads would idle (12.9 -> 15.3 us), in FP64 the
+// registers cost more than the stage (1024: 542 -> 589 us), as in the x passes.
+// Spectra stored in 16 bits keep one order of operations in every pass: another
+// order's last bits move roundings of the stored values, 1e-4 of the field.
+template <typename T, typename S>
+constexpr int col_radix(int L, int NG) {
+    const bool f32 = sizeof(T) == 4 && std::is_same<T, S>::value;
+    return f32 && first_radix(L) == 2 && (NG == 6 ? L >= 128 : L >= 1024) ? 16 : first_radix(L);
+}
 
 template <typename T, typename S, int L, bool INV, int TK, int NG, int NT, bool HALF_IN = false,
           bool HALF_OUT = false>
 struct ColFFT {
     using C = cx<T>;
     using E = typename Spec<T, S>::elem;
+    static constexpr int R0 = col_radix<T, S>(L, NG);
     static constexpr int PN = pack_n<E, TK>();
     using PU = PackU<E, PN>;
     using RW = typename Raw<PN * (int)sizeof(E)>::type;
     static constexpr int NP = TK / PN;  // packs per group row
     static constexpr int W = NG * TK;   // LDS row width (complex)
-    static constexpr int R0 = first_radix(L);
-    static constexpr int NSTAGE = fft_stages(L);
+    static constexpr int NSTAGE = fft_stages(L, R0);
     static constexpr int NU0 = (L / R0) * NG * NP, U0 = (NU0 + NT - 1) / NT;  // stage-0 units per tile / thread
     static constexpr int NU8 = (L / 8) * NG * NP, U8 = (NU8 + NT - 1) / NT;   // radix-8 stage units
     static constexpr int LDS_ELEMS = L * W;
@@ -105,7 +120,7 @@ struct ColFFT {
                 if (HALF_IN && 2 * r >= R0) continue;  // rows >= L/2: zero
                 const int row = t.j + r * (L / R0);
                 const int rowc = row < n_in ? row : n_in - 1;
-                rg.v[m][r].raw = *(const RW*)(gp + (long)rowc * gs);
+                rg.v[m][r].raw = *(const RW*)(gp + row_off(rowc, gs));
                 rg.ok[m][r] = on && row < n_in;
             }
         }
@@ -293,6 +308,58 @@ struct ColFFT {
                 for (int r = 0; r < 8; ++r)
 #pragma unroll
                     for (int q = 0; q < PN; ++q) col[(t.j + r * NS) * W + q] = x[q][r];
+            }
+        }
+    }
+
+    // The stages of the transform with the radix-8 stages first, after its
+    // first one (whose outputs, rows 8 j + r, are in LDS, a barrier before): the
+    // other radix-8 stages, then the radix-R0 stage to global rows < n_out.
+    // NSTAGE >= 2
+    template <int NS>
+    static __device__ __forceinline__ void mid_after(C* buf, const C* __restrict__ tw) {
+        if constexpr (NS * R0 < L) {
+            mid_stage<NS>(buf, tw);
+            mid_after<NS * 8>(buf, tw);
+        }
+    }
+    template <typename Bases>
+    static __device__ __forceinline__ void rest_to_global(C* buf, const C* __restrict__ tw, const Bases& bases,
+                                                          long gs, int n_out, int ncol, int ng, T scale) {
+        mid_after<8>(buf, tw);
+        constexpr int NS = L / R0;
+#pragma unroll
+        for (int m = 0; m < U0; ++m) {
+            const int u = threadIdx.x + m * NT;
+            if (NU0 % NT == 0 || u < NU0) {
+                const Unit t = unit(u);
+                const C* col = buf + t.g * TK + t.p * PN;
+                C x[PN][R0];
+#pragma unroll
+                for (int r = 0; r < R0; ++r) {
+                    const C w = tw[r * t.j];
+#pragma unroll
+                    for (int q = 0; q < PN; ++q) {
+                        const C a = col[(t.j + r * NS) * W + q];
+                        x[q][r] = r == 0 ? a : (INV ? cmulc(a, w) : cmul(a, w));
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < PN; ++q) dft_r<R0, INV>(x[q]);
+                if (t.g < ng && t.p * PN < ncol) {
+                    E* gp = bases(t.g) + t.p * PN + row_off(t.j, gs);
+#pragma unroll
+                    for (int r = 0; r < R0; ++r) {
+                        if (HALF_OUT && 2 * r >= R0) continue;  // rows >= L/2: not wanted
+                        if (t.j + r * NS < n_out) {
+                            PU o;
+#pragma unroll
+                            for (int q = 0; q < PN; ++q)
+                                o.e[q] = Spec<T, S>::put(C{x[q][r].x * scale, x[q][r].y * scale});
+                            *(RW*)(gp + (long)(r * NS) * gs) = o.raw;
+                        }
+                    }
+                }
             }
         }
     }

@@ -7,7 +7,8 @@
 //   v = DFT_R(v)
 //   x'[(j div NS) NS R + k + r NS] = v[r]
 // One stage of radix R0, then radix-8 stages: lengths R0 8^k with R0 = 2, 4, 8,
-// 3, 6, 12, 5, 10 or 20 (first_radix), that is 2^m, 3 2^m and 5 2^m.  The forward transform uses e^{-2 pi i/L}; the inverse
+// 16, 3, 6, 12, 5, 10 or 20 (first_radix, col_radix), that is 2^m, 3 2^m and
+// 5 2^m.  The forward transform uses e^{-2 pi i/L}; the inverse
 // uses e^{+2 pi i/L} and is unnormalised.  Twiddles come from a table
 // tw[m] = e^{-2 pi i m/L}, m < L, built on the host in double precision.
 #pragma once
@@ -100,6 +101,29 @@ template <bool INV, typename C> __device__ __forceinline__ void dft5(C* v) {
     v[3] = csub(b, g);
 }
 
+template <bool INV, typename C> __device__ __forceinline__ void dft16(C* v) {
+    using T = decltype(v[0].x);
+    const T s = T(0.70710678118654752440084436210484903928);
+    const T c1 = T(0.92387953251128675612818318939678828682), s1 = T(0.38268343236508977172845998403039886676);
+    C e[8], o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        e[i] = v[2 * i];
+        o[i] = v[2 * i + 1];
+    }
+    dft8<INV>(e);
+    dft8<INV>(o);
+    const T wx[8] = {T(1), c1, s, s1, T(0), -s1, -s, -c1};
+    const T wy[8] = {T(0), -s1, -s, -c1, T(-1), -c1, -s, -s1};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const C w{wx[k], wy[k]};
+        const C t = k == 0 ? o[0] : k == 4 ? rot90<INV>(o[4]) : INV ? cmulc(o[k], w) : cmul(o[k], w);
+        v[k] = cadd(e[k], t);
+        v[k + 8] = csub(e[k], t);
+    }
+}
+
 template <int R, bool INV, typename C> __device__ __forceinline__ void dft_r(C* v);
 
 // R = A B with A, B coprime, without twiddles (Good and Thomas): input
@@ -131,6 +155,8 @@ template <int R, bool INV, typename C> __device__ __forceinline__ void dft_r(C* 
         dft4<INV>(v[0], v[1], v[2], v[3]);
     } else if constexpr (R == 8) {
         dft8<INV>(v);
+    } else if constexpr (R == 16) {
+        dft16<INV>(v);
     } else if constexpr (R == 3) {
         dft3<INV>(v);
     } else if constexpr (R == 5) {
@@ -155,7 +181,7 @@ constexpr int first_radix(int L) {
     const int m = ilog2(L / odd) % 3;
     return m == 1 ? 2 * odd : m == 2 ? 4 * odd : odd == 1 ? 8 : odd;
 }
-constexpr int fft_stages(int L) { return 1 + ilog2(L / first_radix(L)) / 3; }
+constexpr int fft_stages(int L, int R0) { return 1 + ilog2(L / R0) / 3; }
 
 // The lengths the passes are built for: powers of two and, for spectra stored
 // in the working precision, 3 2^m and 5 2^m from 24 on (those that hold a whole

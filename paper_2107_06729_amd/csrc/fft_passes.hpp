@@ -39,6 +39,12 @@ constexpr int col_tile(int L, int v) {
     const int t = sizeof(T) == 4 ? (L <= 512 ? 16 : 8) : (L <= 512 ? 8 : 4);
     return v == 1 ? (t > 1 ? t / 2 : 1) : v == 2 ? (t > 3 ? t / 4 : 1) : t;
 }
+// Threads of a column tile: 512 where the tile's LDS leaves room for two
+// workgroups a CU at most (FP32 300x300x20, 640 rows of 8 columns: y passes 27.0 and
+// 25.6 us with 256 threads, 25.4 and 24.5 with 512; 1024 rows the same either way);
+// smaller tiles have more workgroups (FP32 256x256x16 at 8 columns 14.9 and 13.9 us
+// with 256 threads, 15.2 and 14.2 with 512)
+constexpr int col_threads(int L, int TK) { return L * TK >= 5120 ? 512 : NT; }
 template <typename T>
 constexpr int zmul_tile(int L, int v) {
     const int t = sizeof(T) == 4 ? (L <= 64 ? 16 : L <= 128 ? 8 : L <= 256 ? 4 : 2)
@@ -414,7 +420,7 @@ __global__ __launch_bounds__(NT) void k_xinv(const typename Spec<T, S>::elem* __
 // LDS of one column-pass tile
 template <typename T, typename S, int L, int TK>
 struct ColShared {
-    using F = ColFFT<T, S, L, false, TK, 1, NT>;
+    using F = ColFFT<T, S, L, false, TK, 1, col_threads(L, TK)>;
     alignas(16) cx<T> buf[F::NSTAGE > 1 ? F::LDS_ELEMS : 1];
     alignas(16) cx<T> twl[L];
 };
@@ -427,7 +433,8 @@ __device__ __forceinline__ void colfft_tile(const typename Spec<T, S>::elem* __r
                                             const cx<T>* __restrict__ tw, T scale, int lin, int ntx, int nby, int nbz,
                                             ColShared<T, S, L, TK>& sh) {
     using C = cx<T>;
-    using F = ColFFT<T, S, L, INV, TK, 1, NT, !INV && HALF, INV && HALF>;
+    constexpr int NTC = col_threads(L, TK);
+    using F = ColFFT<T, S, L, INV, TK, 1, NTC, !INV && HALF, INV && HALF>;
     using E = typename Spec<T, S>::elem;
     // each XCD takes a contiguous run of tiles (xcd_run): when a tile row is
     // shorter than a 128-byte line, the neighbouring tiles that share its
@@ -444,7 +451,7 @@ __device__ __forceinline__ void colfft_tile(const typename Spec<T, S>::elem* __r
     } else {
         C* buf = sh.buf;
         C* twl = sh.twl;
-        TwStage<T, L, NT> tws;
+        TwStage<T, L, NTC> tws;
         tws.fetch(tw);
         F::load_first(rg, sp, s_is, n_in, Kx - kx0, 1);
         tws.put(twl);
@@ -456,7 +463,7 @@ __device__ __forceinline__ void colfft_tile(const typename Spec<T, S>::elem* __r
 }
 
 template <typename T, typename S, int L, bool INV, int TK, bool HALF>
-__global__ __launch_bounds__(NT) void k_colfft(const typename Spec<T, S>::elem* __restrict__ src, long s_cs,
+__global__ __launch_bounds__(col_threads(L, TK)) void k_colfft(const typename Spec<T, S>::elem* __restrict__ src, long s_cs,
                                                long s_os, long s_is, int n_in,
                                                typename Spec<T, S>::elem* __restrict__ dst, long d_cs, long d_os,
                                                long d_is, int n_out, int Kx, const cx<T>* __restrict__ tw,
@@ -482,157 +489,68 @@ struct ZBases {
     E* row1;  // (ky = Py - q, ...)
     unsigned cs;  // component stride nz * nyrows * SX (< 2^31 for every supported mesh)
     __device__ __forceinline__ E* operator()(int g) const {
-        const int c = g >= 3 ? g - 3 : g;
-        return (g >= 3 ? row1 : row0) + (c == 0 ? 0u : c == 1 ? cs : 2u * cs);
+        // one multiply-add; a chain of selects compiles to branches
+        const unsigned c = g >= 3 ? g - 3 : g;
+        return (g >= 3 ? row1 : row0) + (unsigned long)c * cs;
     }
 };
 
-// folded kernel values of columns kx0 .. kx0+TK-1 of row kyf, loaded into
-// registers by load() and written to LDS kl[(kzf * 6 + comp) * TK + col] by
-// put(); columns >= ncol read as zero
-template <typename T, int TK, int KZF>
-struct KernelTile {
-    static constexpr int KB = 16 / (int)sizeof(T);
-    static constexpr bool PACKED = TK % KB == 0;
-    using V = typename Pack<T>::type;  // 16 bytes = KB values
-    static constexpr int NPK = (TK / KB) * KZF * 6;  // packs (PACKED)
-    static constexpr int NE = TK * KZF * 6;          // values (not PACKED)
-    static constexpr int PER = PACKED ? (NPK + NT - 1) / NT : (NE + NT - 1) / NT;
-    typename std::conditional<PACKED, V, T>::type r[PER];
-
-    __device__ __forceinline__ void load(const T* __restrict__ kfold, int kyf, int kx0, int ncol, int SX) {
-#pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int e = threadIdx.x + m * NT;
-            if constexpr (PACKED) {
-                const int b = e / (KZF * 6), rem = e - b * (KZF * 6);
-                r[m] = Pack<T>::zero();
-                if ((NPK % NT == 0 || e < NPK) && b * KB < ncol)
-                    r[m] = *(const V*)(kfold + kernel_index<T>(kyf, kx0 + b * KB, rem / 6, rem % 6, SX, KZF));
-            } else {
-                const int col = e % TK, rem = e / TK;
-                r[m] = T(0);
-                if ((NE % NT == 0 || e < NE) && col < ncol)
-                    r[m] = kfold[kernel_index<T>(kyf, kx0 + col, rem / 6, rem % 6, SX, KZF)];
-            }
-        }
-    }
-    __device__ __forceinline__ void put(T* kl) const {
-#pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int e = threadIdx.x + m * NT;
-            if constexpr (PACKED) {
-                if (NPK % NT == 0 || e < NPK) {
-                    const int b = e / (KZF * 6), rem = e - b * (KZF * 6);
-                    const T* v = (const T*)&r[m];
-#pragma unroll
-                    for (int i = 0; i < KB; ++i) kl[rem * TK + b * KB + i] = v[i];
-                }
-            } else {
-                if (NE % NT == 0 || e < NE) kl[e] = r[m];
-            }
-        }
-    }
-};
-
-template <typename T, int TK, int KZF>
-__device__ __forceinline__ void load_kernel_tile(T* kl, const T* __restrict__ kfold, int kyf, int kx0, int ncol,
-                                                 int SX) {
-    KernelTile<T, TK, KZF> kt;
-    kt.load(kfold, kyf, kx0, ncol, SX);
-    kt.put(kl);
-}
-
-// H = K M on LDS rows: row kz, groups (w, c), TK columns
-template <typename T, int LZ, int TK, int NTH>
-__device__ __forceinline__ void kspace_product(cx<T>* lb, const T* kl, int ng) {
+// H = K M of one (column, kz) with the values k of the folded kernel; yneg and
+// zneg: rows ky > Py/2, kz > Pz/2, where the components odd along that axis
+// change sign
+template <typename T>
+__device__ __forceinline__ void apply_kernel(const T (&k)[6], bool yneg, bool zneg, cx<T>& px, cx<T>& py, cx<T>& pz) {
     using C = cx<T>;
-    constexpr int W = 6 * TK, NU = LZ * 2 * TK, PER = (NU + NTH - 1) / NTH;
-#pragma unroll
-    for (int m = 0; m < PER; ++m) {
-        const int e = threadIdx.x + m * NTH;
-        const int col = e % TK, t = e / TK, w = t & 1, kz = t >> 1;
-        if ((NU % NTH == 0 || e < NU) && 3 * (w + 1) <= ng) {
-            const int kzf = (2 * kz <= LZ) ? kz : LZ - kz;
-            const T sz = (2 * kz > LZ) ? T(-1) : T(1);
-            const T sy = w ? T(-1) : T(1);
-            const T* kp = kl + kzf * 6 * TK + col;
-            const T nxx = kp[0], nyy = kp[TK], nzz = kp[2 * TK];
-            const T nxy = sy * kp[3 * TK], nxz = sz * kp[4 * TK], nyz = sy * sz * kp[5 * TK];
-            C* p = lb + kz * W + w * 3 * TK + col;
-            const C mx = p[0], my = p[TK], mz = p[2 * TK];
-            p[0] = C{nxx * mx.x + nxy * my.x + nxz * mz.x, nxx * mx.y + nxy * my.y + nxz * mz.y};
-            p[TK] = C{nxy * mx.x + nyy * my.x + nyz * mz.x, nxy * mx.y + nyy * my.y + nyz * mz.y};
-            p[2 * TK] = C{nxz * mx.x + nyz * my.x + nzz * mz.x, nxz * mx.y + nyz * my.y + nzz * mz.y};
-        }
-    }
+    const T nxx = k[0], nyy = k[1], nzz = k[2];
+    const T nxy = yneg ? -k[3] : k[3], nxz = zneg ? -k[4] : k[4];
+    const T yz = zneg ? -k[5] : k[5], nyz = yneg ? -yz : yz;
+    const C mx = px, my = py, mz = pz;
+    px = C{nxx * mx.x + nxy * my.x + nxz * mz.x, nxx * mx.y + nxy * my.y + nxz * mz.y};
+    py = C{nxy * mx.x + nyy * my.x + nyz * mz.x, nxy * mx.y + nyy * my.y + nyz * mz.y};
+    pz = C{nxz * mx.x + nyz * my.x + nzz * mz.x, nxz * mx.y + nyz * my.y + nzz * mz.y};
 }
 
-// The same product with the kernel values of each of this thread's product
-// units loaded from global memory into registers (issued early by
-// KernelRegs::load) instead of staged in LDS.  A unit is one (column, kz):
-// it applies the tensor to row ky = q (groups 0..2) and, when the tile holds
-// it, to row ky = Py - q (groups 3..5), whose xy and yz components change
-// sign; so the six values are loaded once for both rows and the ky sign is a
-// negated operand.
-template <typename T, int LZ, int TK, int NTH>
-struct KernelRegs {
-    static constexpr int NU = LZ * TK, PER = (NU + NTH - 1) / NTH;
-    static constexpr int KB = 16 / (int)sizeof(T);
-    T k[PER][6];
-    // A tile may reach past Kx, past the row stride SX, and on the last
-    // folded ky row past the end of kfold: columns >= ncol read column Kx - 1
-    // instead (and units past NU the last unit), so every load stays in
-    // bounds and is issued unconditionally, its value first needed by
-    // product().  Those columns are never stored.
-    __device__ __forceinline__ void load(const T* __restrict__ kfold, int kyf, int kx0, int ncol, int SX, int Kzf) {
-        const T* __restrict__ kb = kfold + kernel_row(kyf, SX, Kzf);  // uniform
-#pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int e0 = threadIdx.x + m * NTH;
-            const int e = (NU % NTH == 0 || e0 < NU) ? e0 : NU - 1;
-            const int col = e % TK, kz = e / TK;
-            const int kzf = (2 * kz <= LZ) ? kz : LZ - kz;
-            const int off = kernel_off<T>(kx0 + (col < ncol ? col : ncol - 1), kzf, 0, Kzf);
-#pragma unroll
-            for (int comp = 0; comp < 6; ++comp) k[m][comp] = kb[off + comp * KB];
-        }
-    }
-    static __device__ __forceinline__ void apply(cx<T>* p, T nxx, T nyy, T nzz, T nxy, T nxz, T nyz) {
-        using C = cx<T>;
-        const C mx = p[0], my = p[TK], mz = p[2 * TK];
-        p[0] = C{nxx * mx.x + nxy * my.x + nxz * mz.x, nxx * mx.y + nxy * my.y + nxz * mz.y};
-        p[TK] = C{nxy * mx.x + nyy * my.x + nyz * mz.x, nxy * mx.y + nyy * my.y + nyz * mz.y};
-        p[2 * TK] = C{nxz * mx.x + nyz * my.x + nzz * mz.x, nxz * mx.y + nyz * my.y + nzz * mz.y};
-    }
-    __device__ __forceinline__ void product(cx<T>* lb, int ng) const {
-        constexpr int W = 6 * TK;
-#pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int e = threadIdx.x + m * NTH;
-            if (NU % NTH == 0 || e < NU) {
-                const int col = e % TK, kz = e / TK;
-                const bool zneg = 2 * kz > LZ;  // the xz and yz components change sign
-                const T nxz = zneg ? -k[m][4] : k[m][4], nyz = zneg ? -k[m][5] : k[m][5];
-                cx<T>* p = lb + kz * W + col;
-                apply(p, k[m][0], k[m][1], k[m][2], k[m][3], nxz, nyz);
-                if (ng == 6) apply(p + 3 * TK, k[m][0], k[m][1], k[m][2], -k[m][3], nxz, -nyz);
-            }
-        }
-    }
-};
+// FP32 z passes with a radix-8 stage take the product in registers between the
+// last forward and the first inverse stage (zmul_tile); in FP64 the thread's
+// values and kernel values fill 230 registers and the waves left hide less than
+// the LDS passes cost (256x256x16 46 us against 41.8, 200x120x10 27.7 against 19.4).
+// FP32, back to back, before and after: 256x256x16 24.8 -> 23.4 us, 128x128x32 19.9 ->
+// 15.8, 200x200x6 15.4 -> 13.2, 128x64x128 (LZ 256) 54 -> 39, 60x60x200 (LZ 512) 92 ->
+// 46 (the last two mostly by zmul_place), 512x512x64 546 -> 526 and BF16 560 -> 463.
+// The pass moves its bytes (within 3 %) at 5.6 TB/s where spectrum B stays in the
+// 256 MB cache in front of HBM and at 3.9 TB/s where it does not (512x512x64: 64-byte
+// rows read and written in place); its vector ALUs are 60-75 % busy.
+template <typename T>
+constexpr bool zmul_in_regs(int LZ) { return sizeof(T) == 4 && LZ >= 16; }
+
+// threads of a z tile: with the product in registers one thread per (ky, column,
+// eight kz) in whole waves, else NT
+template <typename T>
+constexpr int zmul_threads(int LZ, int TK) {
+    if (!zmul_in_regs<T>(LZ)) return NT;
+    const int n = (LZ / 8) * 2 * TK;
+    return n < 64 ? 64 : (n + 63) / 64 * 64;
+}
 
 // LDS of one z-pass tile
 template <typename T, int LZ, int TK>
 struct ZmulShared {
     static constexpr int L = LZ > 1 ? LZ : 2;
-    static constexpr int KZF = LZ / 2 + 1;
     alignas(16) cx<T> lb[LZ * 6 * TK];
-    alignas(16) T kl[LZ == 1 ? KZF * 6 * TK : 1];
     alignas(16) cx<T> twl[L];
 };
 
 // kx tile `tile`, folded row pair q, sample `sample`
+//
+// FP32, lengths of 16 and more: the last forward stage (radix 8, outputs kz = j + r
+// LZ/8) and the first inverse stage (radix 8 with inputs j + r LZ/8, or radix R0
+// with inputs j' + q LZ/R0, 8/R0 of its butterflies) take the same elements, so one
+// thread does both and the product between them in registers, for the three
+// components of one (ky, column, j).  The tile then crosses the LDS four times
+// (eight with a third stage) instead of eight to twelve.  The thread's 8 x 6 kernel
+// values are loaded with the tile, whole packs a lane.  The inverse starts with
+// radix 8 where the spectra are stored in FP32; 16-bit spectra keep the order
+// of the other passes (R0 first; col_radix), bit for bit that of the tile in LDS.
 template <typename T, typename S, int LZ, int TK>
 __device__ __forceinline__ void zmul_tile(typename Spec<T, S>::elem* __restrict__ buf, int SX, int Kx, int nz,
                                           int nyrows, int Py, const T* __restrict__ kfold,
@@ -642,12 +560,12 @@ __device__ __forceinline__ void zmul_tile(typename Spec<T, S>::elem* __restrict_
     using E = typename Spec<T, S>::elem;
     constexpr int L = LZ > 1 ? LZ : 2;  // LZ = 1 uses no transform
     constexpr int KZF = LZ / 2 + 1;
+    constexpr int NTZ = zmul_threads<T>(LZ, TK), W = 6 * TK;
     // rows z >= nz of the forward input are the zero padding and only rows
     // z < nz of the inverse output are kept; nz <= Pz/2 always
-    using Ff = ColFFT<T, S, L, false, TK, 6, NT, true, false>;
-    using Fi = ColFFT<T, S, L, true, TK, 6, NT, false, true>;
+    using Ff = ColFFT<T, S, L, false, TK, 6, NTZ, true, false>;
+    using Fi = ColFFT<T, S, L, true, TK, 6, NTZ, false, true>;
     C* lb = sh.lb;
-    T* kl = sh.kl;
     C* twl = sh.twl;
     const int kx0 = tile * TK;
     const int ng = (2 * q == Py || q == 0) ? 3 : 6;  // 0 <= q <= Py/2
@@ -655,78 +573,175 @@ __device__ __forceinline__ void zmul_tile(typename Spec<T, S>::elem* __restrict_
     const long cs = (long)nz * nyrows * SX, zs = (long)nyrows * SX;
     E* sb = buf + (long)sample * 3 * cs;
     const ZBases<E> bases{sb + (long)q * SX + kx0, sb + (long)(Py - q) * SX + kx0, (unsigned)cs};
-    if constexpr (LZ == 1) {
-        // no z transform: load the 6 x TK values, multiply, store
-        using PU = typename Ff::PU;
-        using RW = typename Ff::RW;
-        constexpr int PN = Ff::PN, NU = 6 * (TK / PN);
-        for (int u = threadIdx.x; u < NU; u += NT) {
-            const int p = u % (TK / PN), g = u / (TK / PN);
-            if (g < ng && p * PN < ncol) {
-                PU v;
-                v.raw = *(const RW*)(bases(g) + p * PN);
-#pragma unroll
-                for (int i = 0; i < PN; ++i) lb[g * TK + p * PN + i] = Spec<T, S>::get(v.e[i]);
-            }
-        }
-        load_kernel_tile<T, TK, KZF>(kl, kfold, q, kx0, ncol, SX);
-        __syncthreads();
-        kspace_product<T, 1, TK, NT>(lb, kl, ng);
-        __syncthreads();
-        for (int u = threadIdx.x; u < NU; u += NT) {
-            const int p = u % (TK / PN), g = u / (TK / PN);
-            if (g < ng && p * PN < ncol) {
-                PU v;
-#pragma unroll
-                for (int i = 0; i < PN; ++i) v.e[i] = Spec<T, S>::put(lb[g * TK + p * PN + i]);
-                *(RW*)(bases(g) + p * PN) = v.raw;
-            }
-        }
-    } else {
-        TwStage<T, LZ, NT> tws;
+    const T* __restrict__ krow = kfold + kernel_row(q, SX, KZF);  // uniform
+    // A tile may reach past Kx: columns >= ncol read the kernel of column Kx - 1
+    // instead, so every load stays in bounds and is issued unconditionally.
+    // Those columns are never stored.
+    auto kcol = [&](int col) { return kx0 + (col < ncol ? col : ncol - 1); };
+    if constexpr (zmul_in_regs<T>(LZ)) {
+        constexpr int L8 = LZ / 8, NU = L8 * 2 * TK;
+        TwStage<T, LZ, NTZ> tws;
         tws.fetch(tw);
         typename Ff::Regs rg;
         Ff::load_first(rg, bases, zs, nz, ncol, ng);
-        KernelRegs<T, LZ, TK, NT> kr;
-        kr.load(kfold, q, kx0, ncol, SX, KZF);
+        const bool live = NU % NTZ == 0 || (int)threadIdx.x < NU;
+        const int e = live ? threadIdx.x : NU - 1;
+        const int col = e % TK, w = (e / TK) & 1, j = e / (2 * TK);
+        const int kc = kcol(col);
+        T k[8][6];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int kz = j + r * L8;  // j < L8: above LZ/2 for r > 4, and for r = 4 unless j = 0
+            kernel_load<T>(krow, kc, r < 4 || (r == 4 && j == 0) ? kz : LZ - kz, SX, k[r]);
+        }
         tws.put(twl);
         Ff::first_to_lds(rg, lb);
         __syncthreads();
-        if constexpr (Ff::NSTAGE > 1) {
-            Ff::middle(lb, twl);
-            Ff::last_in_lds(lb, twl);
-            __syncthreads();
+        Ff::middle(lb, twl);
+        C v[3][8];
+        C* p = lb + w * 3 * TK + col;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const C t = twl[r * j];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const C a = p[(j + r * L8) * W + c * TK];
+                v[c][r] = r == 0 ? a : cmul(a, t);
+            }
         }
-        kr.product(lb, ng);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) dft8<false>(v[c]);
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+            apply_kernel(k[r], w != 0, r > 4 || (r == 4 && j != 0), v[0][r], v[1][r], v[2][r]);
+        constexpr int IR = std::is_same<T, S>::value ? 8 : Fi::R0, NB = 8 / IR;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                C x[IR];
+#pragma unroll
+                for (int i = 0; i < IR; ++i) x[i] = v[c][b + i * NB];
+                dft_r<IR, true>(x);
+#pragma unroll
+                for (int i = 0; i < IR; ++i) v[c][b + i * NB] = x[i];
+            }
         __syncthreads();
-        Fi::first_in_lds(lb);
+        if (live) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int i = 0; i < IR; ++i) p[((j + b * L8) * IR + i) * W + c * TK] = v[c][b + i * NB];
+        }
+        __syncthreads();
+        if constexpr (std::is_same<T, S>::value) {
+            Fi::rest_to_global(lb, twl, bases, zs, nz, ncol, ng, T(1));
+        } else {
+            Fi::middle(lb, twl);
+            Fi::last_to_global(lb, twl, bases, zs, nz, ncol, ng, T(1));
+        }
+    } else {
+        // the transform in LDS in natural order, the kernel values of this
+        // thread's product units (both ky rows of a column and kz) in registers
+        using PU = typename Ff::PU;
+        using RW = typename Ff::RW;
+        constexpr int PN = Ff::PN;
+        constexpr int NUP = LZ * TK, PER = (NUP + NTZ - 1) / NTZ;
+        T k[PER][6];
+        auto load_k = [&]() {
+#pragma unroll
+            for (int m = 0; m < PER; ++m) {
+                const int e0 = threadIdx.x + m * NTZ, e = e0 < NUP ? e0 : NUP - 1;
+                const int kz = e / TK;
+                kernel_load<T>(krow, kcol(e % TK), 2 * kz <= LZ ? kz : LZ - kz, SX, k[m]);
+            }
+        };
+        if constexpr (LZ == 1) {
+            constexpr int NU = 6 * (TK / PN);
+            load_k();
+            for (int u = threadIdx.x; u < NU; u += NTZ) {
+                const int p = u % (TK / PN), g = u / (TK / PN);
+                if (g < ng && p * PN < ncol) {
+                    PU v;
+                    v.raw = *(const RW*)(bases(g) + p * PN);
+#pragma unroll
+                    for (int i = 0; i < PN; ++i) lb[g * TK + p * PN + i] = Spec<T, S>::get(v.e[i]);
+                }
+            }
+        } else {
+            TwStage<T, LZ, NTZ> tws;
+            tws.fetch(tw);
+            typename Ff::Regs rg;
+            Ff::load_first(rg, bases, zs, nz, ncol, ng);
+            load_k();
+            tws.put(twl);
+            Ff::first_to_lds(rg, lb);
+            if constexpr (Ff::NSTAGE > 1) {
+                __syncthreads();
+                Ff::middle(lb, twl);
+                Ff::last_in_lds(lb, twl);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < PER; ++m) {
+            const int e = threadIdx.x + m * NTZ;
+            if (NUP % NTZ == 0 || e < NUP) {
+                const int kz = e / TK;
+                const bool zneg = 2 * kz > LZ;
+                C* p = lb + kz * W + e % TK;
+                apply_kernel(k[m], false, zneg, p[0], p[TK], p[2 * TK]);
+                if (ng == 6) apply_kernel(k[m], true, zneg, p[3 * TK], p[4 * TK], p[5 * TK]);
+            }
+        }
+        __syncthreads();
+        if constexpr (LZ > 1) Fi::first_in_lds(lb);
         if constexpr (Fi::NSTAGE > 1) {
             Fi::middle(lb, twl);
             Fi::last_to_global(lb, twl, bases, zs, nz, ncol, ng, T(1));
-        } else {
-            // single-stage lengths: rows z < nz from LDS
-            using PU = typename Ff::PU;
-            using RW = typename Ff::RW;
-            constexpr int PN = Ff::PN, NU = LZ * 6 * (TK / PN);
-            for (int u = threadIdx.x; u < NU; u += NT) {
-                const int p = u % (TK / PN), t = u / (TK / PN), g = t % 6, z = t / 6;
-                if (g < ng && p * PN < ncol && z < nz) {
-                    PU v;
+            return;
+        }
+        constexpr int NU = LZ * 6 * (TK / PN);
+        for (int u = threadIdx.x; u < NU; u += NTZ) {
+            const int p = u % (TK / PN), t = u / (TK / PN), g = t % 6, z = t / 6;
+            if (g < ng && p * PN < ncol && z < nz) {
+                PU v;
 #pragma unroll
-                    for (int i = 0; i < PN; ++i) v.e[i] = Spec<T, S>::put(lb[z * 6 * TK + g * TK + p * PN + i]);
-                    *(RW*)(bases(g) + z * zs + p * PN) = v.raw;
-                }
+                for (int i = 0; i < PN; ++i) v.e[i] = Spec<T, S>::put(lb[z * W + g * TK + p * PN + i]);
+                *(RW*)(bases(g) + z * zs + p * PN) = v.raw;
             }
         }
     }
 }
 
+// Tiles of one 128-byte line of a spectrum row (G of them when a tile row is
+// shorter) are placed on one XCD, one dispatch round apart, so the line is
+// fetched into one L2: position lin of ntile x nq (ntile a multiple of G, XCD
+// lin % 8) -> tile and row pair.
+template <typename E, int TK>
+constexpr int zmul_group() { return TK * (int)sizeof(E) >= 128 ? 1 : 128 / (TK * (int)sizeof(E)); }
+template <typename E, int TK>
+__device__ __forceinline__ void zmul_place(int lin, int ntile, int nq, int& tile, int& q) {
+    constexpr int G = zmul_group<E, TK>(), B = 8 * G;
+    if (G > 1 && lin < ntile * nq / B * B) {
+        const int r = lin % B;
+        lin = lin - r + (r % 8) * G + r / 8;
+    }
+    q = lin / ntile;
+    tile = lin - q * ntile;
+}
+
 template <typename T, typename S, int LZ, int TK>
-__global__ __launch_bounds__(NT) void k_zmul(typename Spec<T, S>::elem* __restrict__ buf, int SX, int Kx, int nz,
+__global__ __launch_bounds__(zmul_threads<T>(LZ, TK)) void k_zmul(typename Spec<T, S>::elem* __restrict__ buf, int SX, int Kx, int nz,
                                              int nyrows, int Py, const T* __restrict__ kfold,
                                              const cx<T>* __restrict__ tw) {
     __shared__ ZmulShared<T, LZ, TK> sh;
-    zmul_tile<T, S, LZ, TK>(buf, SX, Kx, nz, nyrows, Py, kfold, tw, blockIdx.x, blockIdx.y, blockIdx.z, sh);
+    int tile, q;
+    zmul_place<typename Spec<T, S>::elem, TK>(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x, gridDim.y, tile, q);
+    if (tile * TK >= Kx) return;
+    zmul_tile<T, S, LZ, TK>(buf, SX, Kx, nz, nyrows, Py, kfold, tw, tile, q, blockIdx.z, sh);
 }
 
 }  // namespace llgx

@@ -26,7 +26,7 @@ template <typename T, int L, bool INV, int NR, int NT, bool HALF_IN = false, boo
 struct RowFFT {
     using C = cx<T>;
     static constexpr int R0 = first_radix(L);
-    static constexpr int NSTAGE = fft_stages(L);
+    static constexpr int NSTAGE = fft_stages(L, R0);
     static constexpr int RS = L + L / 8 + 1;  // padded row stride (complex)
     static constexpr int LDS_ELEMS = NR * RS;
     static constexpr int NU0 = NR * (L / R0), U0 = (NU0 + NT - 1) / NT;

@@ -154,20 +154,38 @@ template <typename T>
 hipError_t launch_fold(hipStream_t s, const cx<double>* spec, int SX, int Kx, int Py, int Pz, int Kyf, int Kzf,
                        double scale, int comp, T* kfold, T* kcol, int KYS, double* imag_max_parts, int nparts);
 
-// Folded k-space kernel layout: blocks of KB = 16 / sizeof(T) adjacent kx,
-// each block holding all (kz, component) values of one ky, so the z pass
-// reads a tile's kernel values as contiguous 16-byte packs.
+// Folded k-space kernel layout: for each (ky, kz) the six components of SX
+// columns in planes of 16-byte packs, FP32 [kx][xx yy zz xy] and [kx][xz yz] (8
+// bytes), FP64 [kx][xx yy], [kx][zz xy], [kx][xz yz].  A lane per column reads
+// whole packs and consecutive columns are contiguous; a tile of 16 FP32 (8
+// FP64) columns reads whole 128-byte lines of every plane.
 // kernel_index = kernel_row (start of the ky row, 64-bit) + kernel_off (within
 // the row, < 6 Kzf SX, 32-bit).
 __host__ __device__ __forceinline__ long kernel_row(int kyf, int SX, int Kzf) { return (long)kyf * SX * Kzf * 6; }
 template <typename T>
-__host__ __device__ __forceinline__ int kernel_off(int kx, int kzf, int comp, int Kzf) {
-    constexpr int KB = 16 / (int)sizeof(T);
-    return (((kx / KB) * Kzf + kzf) * 6 + comp) * KB + kx % KB;
+__host__ __device__ __forceinline__ int kernel_off(int kx, int kzf, int comp, int SX) {
+    const int row = kzf * SX * 6;
+    if (sizeof(T) == 8) return row + (comp / 2) * SX * 2 + kx * 2 + comp % 2;
+    return comp < 4 ? row + kx * 4 + comp : row + SX * 4 + kx * 2 + comp - 4;
 }
 template <typename T>
 __host__ __device__ __forceinline__ long kernel_index(int kyf, int kx, int kzf, int comp, int SX, int Kzf) {
-    return kernel_row(kyf, SX, Kzf) + kernel_off<T>(kx, kzf, comp, Kzf);
+    return kernel_row(kyf, SX, Kzf) + kernel_off<T>(kx, kzf, comp, SX);
+}
+// the six components of one (ky, kz, column): off = kernel_off(kx, kzf, 0, SX)
+template <typename T>
+__device__ __forceinline__ void kernel_load(const T* __restrict__ row, int kx, int kzf, int SX, T (&k)[6]) {
+    if constexpr (sizeof(T) == 4) {
+        const float4 a = *(const float4*)(row + kernel_off<T>(kx, kzf, 0, SX));
+        const float2 b = *(const float2*)(row + kernel_off<T>(kx, kzf, 4, SX));
+        k[0] = a.x, k[1] = a.y, k[2] = a.z, k[3] = a.w, k[4] = b.x, k[5] = b.y;
+    } else {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const double2 a = *(const double2*)(row + kernel_off<T>(kx, kzf, 2 * p, SX));
+            k[2 * p] = a.x, k[2 * p + 1] = a.y;
+        }
+    }
 }
 
 // Launch variants per FFT pass (bit-identical results, different tiles).

@@ -17,7 +17,7 @@ hipError_t launch_colfft(hipStream_t s, int L, bool inv, SpecPtr src, long s_cs,
     // the tensor setup transforms whole padded columns
     const bool half = inv ? 2 * n_out <= L : 2 * n_in <= L;
 #define CF_H(LL, TK, INV, H)                                                                                 \
-    k_colfft<T, S, LL, INV, TK, H><<<g, NT, 0, s>>>(sp, s_cs, s_os, s_is, n_in, dp, d_cs, d_os, d_is, n_out, Kx, \
+    k_colfft<T, S, LL, INV, TK, H><<<g, col_threads(LL, TK), 0, s>>>(sp, s_cs, s_os, s_is, n_in, dp, d_cs, d_os, d_is, n_out, Kx, \
                                                     tw, scale)
 #define CF_T(LL, TK)                                                                   \
     {                                                                                  \

@@ -20,9 +20,8 @@
 // In LDS each (component, z, column) is one padded row of the y transform
 // (RowFFT's layout); the z transform of a (column, ky) is in one thread's
 // registers, and its three components meet there for the product.
-// The arithmetic is that of ColFFT and zmul_tile, operation for operation, so
-// spectra stored in the working precision give the same bits as the separate
-// passes (16-bit spectra skip the rounding of spectrum B).
+// The arithmetic is that of ColFFT and zmul_tile, operation for operation, with
+// 16-bit spectra rounded where the separate passes store them: the same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -138,10 +137,9 @@ __global__ __launch_bounds__(NTH) void k_yzy(typename Spec<T, S>::elem* __restri
                     continue;
                 }
                 v[a][z] = col[(a * NZ + z) * TK * Ff::RS];
-                if constexpr (!std::is_same<T, S>::value) {
-                    v[a][z].x *= yscale;
-                    v[a][z].y *= yscale;
-                }
+                // 16-bit spectra: rounded where the separate passes store them
+                if constexpr (!std::is_same<T, S>::value)
+                    v[a][z] = Spec<T, S>::get(Spec<T, S>::put(C{v[a][z].x * yscale, v[a][z].y * yscale}));
             }
         if constexpr (LZ > 1) {
 #pragma unroll
@@ -168,7 +166,8 @@ __global__ __launch_bounds__(NTH) void k_yzy(typename Spec<T, S>::elem* __restri
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int z = 0; z < NZ; ++z) col[(a * NZ + z) * TK * Ff::RS] = v[a][z];
+            for (int z = 0; z < NZ; ++z)
+                col[(a * NZ + z) * TK * Ff::RS] = Spec<T, S>::get(Spec<T, S>::put(v[a][z]));
     }
     __syncthreads();
     // y inverse, the last stage to global memory

@@ -17,8 +17,9 @@ hipError_t launch_zmul(hipStream_t s, int LZ, SpecPtr buf, int SX, int Kx, int n
     if (!row_off_ok(LZ, (long)nyrows * SX) || (long)nz * nyrows * SX >= (1L << 31)) return hipErrorInvalidValue;
 #define ZM_T(LL, TK)                                                                                \
     {                                                                                               \
-        dim3 g((unsigned)((Kx + TK - 1) / TK), (unsigned)(Py / 2 + 1), (unsigned)nb);               \
-        k_zmul<T, S, LL, TK><<<g, NT, 0, s>>>(bp, SX, Kx, nz, nyrows, Py, kfold, tw);                 \
+        constexpr int G = zmul_group<E, TK>();                                                      \
+        dim3 g((unsigned)((Kx + TK * G - 1) / (TK * G) * G), (unsigned)(Py / 2 + 1), (unsigned)nb); \
+        k_zmul<T, S, LL, TK><<<g, zmul_threads<T>(LL, TK), 0, s>>>(bp, SX, Kx, nz, nyrows, Py, kfold, tw);                 \
     }
 #define ZM(LL)                                          \
     case LL: {                                          \
