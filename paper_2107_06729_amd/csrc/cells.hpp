@@ -349,6 +349,119 @@ __device__ __forceinline__ void stage_final_block(const Combo<T>& mk, const Extr
     if (tid == 0) parts[k.by * k.gx + k.bx] = bm;
 }
 
+// ---------------------------------------------------------------------------
+// Whole sub-steps for small meshes (stage_direct_ok): the stage input M_k of
+// Eq. (4) is formed at every stencil read and Eq. (6) at the stage's own time
+// from the stored fields, so a sub-step is one launch with no stage input and
+// no Eq. (6) field in memory.  The sums are those of combine_* and epoly_*,
+// term for term: the same bits.
+
+// M_k at flat index i of the sample's [3][N] block (NF terms)
+template <typename T, int NF>
+struct ComboField {
+    const Combo<T>& c;
+    long off;
+    __device__ __forceinline__ T operator()(long i) const {
+        T v = c.base[off + i];
+#pragma unroll
+        for (int l = 0; l < NF; ++l) v += c.coef[l] * c.f[l][off + i];
+        return v;
+    }
+};
+
+// F of the sub-step; NG: at most this many Eq. (6) nodes (loads past ex.n read
+// node 0 and are left out of the sum)
+template <typename T, int NF, int NG>
+__device__ __forceinline__ void stage_direct_rhs(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                                 const CellIdx& ci, long N, T m[3], T f[3]) {
+    const long i0 = ci.off + ci.cell;
+    T gk[NG][3];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        const T* p = ex.g[i < ex.n ? i : 0];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) gk[i][c] = p[i0 + c * N];
+    }
+    const ComboField<T, NF> M{mk, ci.off};
+    T hd[3], H[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        T g = NG == 1 ? gk[0][c] : T(0);
+        if constexpr (NG > 1) {
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const T s = g + ex.w[i] * gk[i][c];
+                g = i < ex.n ? s : g;
+            }
+        }
+        hd[c] = -ph.n00[c] * M(c * N + ci.cell) + T(1) * g;
+    }
+    heff_at(M, N, ci.cell, ci.x, ci.y, ci.z, ci.b, ph, hd, m, H);
+    llg_at(m, H, ph, f);
+}
+
+template <typename T, int NF, int NG>
+__device__ __forceinline__ void stage_direct_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                                   T* __restrict__ F, const CellBlk& k) {
+    const long N = (long)ph.nx * ph.ny * ph.nz;
+    const CellIdx ci = cell_index(ph, k);
+    if (!ci.ok) return;
+    T m[3], f[3];
+    stage_direct_rhs<T, NF, NG>(mk, ex, ph, ci, N, m, f);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) F[ci.off + c * N + ci.cell] = f[c];
+}
+
+// the last sub-step with Eq. (3) and the estimate (stage_final_block).  mnew may
+// be M0, but not mk's base or one of its terms: neighbours still read those.
+template <typename T, int NF, int NG>
+__device__ __forceinline__ void stage_direct_final_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                                         const T* M0, const Final<T>& fs, double inv_ms,
+                                                         T* mnew, double* __restrict__ parts, const CellBlk& k) {
+    const long N = (long)ph.nx * ph.ny * ph.nz;
+    const CellIdx ci = cell_index(ph, k);
+    const int tid = k.iy * k.tx + k.ix;
+    double emax = 0.0;
+    if (ci.ok) {
+        const long i0 = ci.off + ci.cell;
+        constexpr int NS = MAX_F - 1;  // stored derivatives, the last entry is this stage's own
+        T m0[3], f[NS][3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m0[c] = M0[i0 + c * N];
+#pragma unroll
+        for (int l = 0; l < NS; ++l) {
+            const T* p = l < fs.n - 1 ? fs.f[l] : M0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f[l][c] = p[i0 + c * N];
+        }
+        T m[3], fS[3];
+        stage_direct_rhs<T, NF, NG>(mk, ex, ph, ci, N, m, fS);
+        double e2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            T v = m0[c];
+            double d = 0.0;
+#pragma unroll
+            for (int l = 0; l < NS; ++l) {
+                const T s = v + fs.cb[l] * f[l][c];
+                const double e = d + fs.ce[l] * (double)f[l][c];
+                v = l < fs.n - 1 ? s : v;
+                d = l < fs.n - 1 ? e : d;
+            }
+            v += fs.cb[fs.n - 1] * fS[c];
+            mnew[i0 + c * N] = v;
+            if (fs.err) {
+                d += fs.ce[fs.n - 1] * (double)fS[c];
+                e2 += d * d;
+            }
+        }
+        emax = sqrt(e2) * inv_ms;
+        if (e2 != e2) emax = e2;
+    }
+    const double bm = block_max(emax, tid);
+    if (tid == 0) parts[k.by * k.gx + k.bx] = bm;
+}
+
 template <typename T, int NF>
 __device__ __forceinline__ void final_blocks(long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms,
                                              T* mnew, double* __restrict__ parts, int blk, int nblk) {

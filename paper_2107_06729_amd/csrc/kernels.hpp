@@ -222,6 +222,14 @@ hipError_t launch_stage_ep(hipStream_t s, const Combo<T>& mk, const Extrap<T>& e
 template <typename T>
 hipError_t launch_stage_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, const T* M0,
                               const Final<T>& fs, double inv_ms, T* mnew, double* parts);
+// Sub-steps of small meshes, stage input and Eq. (6) field formed inside
+// (cells.hpp): mk with its terms, ex.n nodes of the stage's own time
+bool stage_direct_ok(long cells, size_t real_bytes, int terms);
+template <typename T>
+hipError_t launch_stage_direct(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F);
+template <typename T>
+hipError_t launch_stage_direct_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                     const T* M0, const Final<T>& fs, double inv_ms, T* mnew, double* parts);
 template <typename T>
 hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms, T* mnew,
                         double* parts, int nparts);

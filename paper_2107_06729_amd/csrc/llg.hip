@@ -49,6 +49,22 @@ __global__ __launch_bounds__(NTS) void k_epoly_scalar(long n, EPoly<T> ep) {
     epoly_scalar_blocks<T, NG>(n, ep, blockIdx.x, gridDim.x);
 }
 
+template <typename T, int NF, int NG>
+__global__ __launch_bounds__(NTS) void k_stage_direct(Combo<T> mk, Extrap<T> ex, Phys<T> ph, T* __restrict__ F, int tx,
+                                                      int ry) {
+    stage_direct_block<T, NF, NG>(mk, ex, ph, F, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
+                                                         (int)threadIdx.x, (int)threadIdx.y});
+}
+
+template <typename T, int NF, int NG>
+__global__ __launch_bounds__(NTS) void k_stage_direct_final(Combo<T> mk, Extrap<T> ex, Phys<T> ph, const T* M0,
+                                                            Final<T> fs, double inv_ms, T* mnew,
+                                                            double* __restrict__ parts, int tx, int ry) {
+    stage_direct_final_block<T, NF, NG>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,
+                                        CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
+                                                (int)threadIdx.x, (int)threadIdx.y});
+}
+
 // 2-D grid of the stencil kernels: blockIdx.x over row groups, blockIdx.y
 // over x segments, blocks of tx x ry threads.  The block shape comes in as an
 // argument: reading blockDim costs a vector load from the dispatch packet
@@ -305,6 +321,56 @@ hipError_t launch_stage_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>
     return hipGetLastError();
 }
 
+// Sub-steps with at most two terms are faster in one launch at every size (ABM2
+// p = 2, whole adaptive steps: 32x32x2 58.7 -> 30.1 us, 256x256x16 135.6 -> 126.8 FP32).
+// With more, each term is read again at the neighbours, which pays while the
+// fields stay near the CU and the launches saved (12 of 23 in a Dormand-Prince
+// step) count: up to 512 KiB a component.  RKDP54 p = 4, whole steps with and
+// without: 256x64x1 FP32 64 / 86 us, 256x256x2 79 / 97, 256x256x4 102 / 98,
+// 128x128x32 202 / 159; FP64 128x128x4 77 / 91, 256x256x2 113 / 102.
+bool stage_direct_ok(long cells, size_t real_bytes, int terms) {
+    return terms <= 2 || cells * (long)real_bytes <= (512L << 10);
+}
+
+#define DIRECT_CASES(M) \
+    M(0, 1) M(1, 1) M(2, 1) M(3, 1) M(4, 1) M(5, 1) M(6, 1) M(7, 1) M(0, 6) M(1, 6) M(2, 6) M(3, 6) M(4, 6) M(5, 6) \
+        M(6, 6) M(7, 6)
+
+template <typename T>
+hipError_t launch_stage_direct(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F) {
+    const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
+    const int tx = (int)cg.block.x, ry = (int)cg.block.y;
+    if (ex.n < 1 || ex.n > MAX_HIST) return hipErrorInvalidValue;
+    const int ng = ex.n == 1 ? 1 : 6;
+#define SD(K, G)                                                                             \
+    if (mk.nf == K && ng == G) {                                                             \
+        k_stage_direct<T, K, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, tx, ry);         \
+        return hipGetLastError();                                                            \
+    }
+    DIRECT_CASES(SD)
+#undef SD
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_stage_direct_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                     const T* M0, const Final<T>& fs, double inv_ms, T* mnew, double* parts) {
+    const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
+    const int tx = (int)cg.block.x, ry = (int)cg.block.y;
+    if (ex.n < 1 || ex.n > MAX_HIST || fs.n < 1 || fs.n > MAX_F || mnew == mk.base) return hipErrorInvalidValue;
+    const int ng = ex.n == 1 ? 1 : 6;
+#define SD(K, G)                                                                                            \
+    if (mk.nf == K && ng == G) {                                                                            \
+        k_stage_direct_final<T, K, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, M0, fs, inv_ms, mnew, parts, \
+                                                                   tx, ry);                                 \
+        return hipGetLastError();                                                                           \
+    }
+    DIRECT_CASES(SD)
+#undef SD
+    return hipErrorInvalidValue;
+}
+#undef DIRECT_CASES
+
 template <typename T>
 hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms, T* mnew,
                         double* parts, int nparts) {
@@ -365,6 +431,10 @@ hipError_t launch_cast(hipStream_t s, long n, const double* src, T* dst) {
 }
 
 #define INST(T)                                                                                                  \
+    template hipError_t launch_stage_direct<T>(hipStream_t, const Combo<T>&, const Extrap<T>&, const Phys<T>&, T*); \
+    template hipError_t launch_stage_direct_final<T>(hipStream_t, const Combo<T>&, const Extrap<T>&,             \
+                                                     const Phys<T>&, const T*, const Final<T>&, double, T*,      \
+                                                     double*);                                                   \
     template hipError_t launch_combine<T>(hipStream_t, long, const Combo<T>&, T*);                               \
     template hipError_t launch_epoly<T>(hipStream_t, long, const EPoly<T>&);                                     \
     template hipError_t launch_extrap_rhs<T>(hipStream_t, const Combo<T>&, const Extrap<T>&, const Phys<T>&, T*,   \

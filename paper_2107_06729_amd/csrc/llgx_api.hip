@@ -126,10 +126,13 @@ struct Ctx {
     int nparts = 1;             // blocks of the 1-D reduction kernels
     long nparts_alloc = 1;      // capacity of parts (also covers the 2-D cell grid)
     double* scal = nullptr;     // [0] error norm, [1..3] sums for <M>
-    int* empty_flag = nullptr;  // device: [0] some cell of M has M = 0; [1] the same for the
-                                // input of a field call (llgx_demag / heff / rhs)
-    bool field_input = false;   // phys() reads flag [1] (during a field call)
-    const int* empty_use = nullptr;  // when set, phys() reads this flag instead
+    double* err_host = nullptr; // the error norm in pinned host memory (adaptive steps), written by
+    double* err_dev = nullptr;  // the reduction through its device address
+    int* empty_flag = nullptr;  // device: [0] some cell of M has M = 0; [1] always 1
+    bool empty_stale = false;   // M changed since the flag was set (batches: see check_stepper)
+    // during a field call: flag [1], so every neighbour is tested (the same result;
+    // a look at the input first was two launches, a third of a small mesh's call)
+    bool field_input = false;
     void* spec_use[2] = {nullptr, nullptr};  // when set, the spectra A and B of the passes
     void* noalloc = nullptr;    // device address of this device's llgx_demag_noalloc scratch
     double* octant = nullptr;   // real-space tensor for offsets 0..n-1 (double)
@@ -665,6 +668,16 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     std::vector<double> times;
     std::vector<int> field_of(tab->S, -1);
     bool fuse_ep = false;
+    // sub-steps in one launch each, unless the stage inputs are all chained and
+    // the first sub-step forms the Eq. (6) fields (RK4: as few launches already)
+    int terms = 0;  // most terms of a stage input that is not chained
+    for (int k = 1; k < tab->S; ++k) {
+        int nf = 0;
+        for (int l = 0; l < k; ++l) nf += tab->a[k][l] != 0.0;
+        if (!chained(k)) terms = std::max(terms, nf);
+    }
+    const bool direct = pl.extrap && !c->rec && (terms > 0 || tab->S < 3) &&
+                        stage_direct_ok(c->ncell * c->nb, sizeof(T), terms);
     EPoly<T> ep_fused{};
     if (pl.extrap) {
         for (auto& hh : c->hist) {
@@ -684,7 +697,7 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             }
             field_of[k] = j;
         }
-        if (!times.empty()) {
+        if (!times.empty() && !direct) {
             EPoly<T> ep{};
             ep.ng = (int)nodes.size();
             ep.nd = (int)times.size();
@@ -736,7 +749,38 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             cb.coef[cb.nf] = (T)(h * tab->a[k][l]);
             cb.nf++;
         }
-        if (pl.extrap) {
+        if (direct) {
+            Extrap<T> ex{};
+            ex.n = 1;
+            ex.w[0] = T(1);
+            ex.g[0] = (const T*)c->G[pl.slot0];
+            if (field_of[k] >= 0) {
+                ex.n = (int)nodes.size();
+                const std::vector<double> w = lagrange(nodes, tab->c[k] * h);
+                for (int i = 0; i < ex.n; ++i) {
+                    ex.g[i] = (const T*)c->G[slots[i]];
+                    ex.w[i] = (T)w[i];
+                }
+            }
+            const bool last = k == tab->S - 1;
+            if (formed[k]) {
+                cb = plain<T>(mkbuf(k));
+            } else if (last && pl.in_place) {
+                // Eq. (3) overwrites M0, which the stage input's neighbours would read
+                PROF(LLGX_K_COMBINE);
+                HIPCHK(c, launch_combine<T>(c->stream, 3 * c->ncell * c->nb, cb, (T*)mkbuf(k)));
+                cb = plain<T>(mkbuf(k));
+            }
+            ProfScope ps(c, last ? LLGX_K_FINAL : LLGX_K_EXTRAP);
+            if (last) {
+                add_final(k);  // own derivative, last entry
+                HIPCHK(c, launch_stage_direct_final<T>(c->stream, cb, ex, phys<T>(c), (const T*)c->M, fs, 1.0 / c->p.Ms,
+                                                       (T*)(pl.in_place ? c->M : c->Mnew), c->parts));
+                fused_final = true;
+            } else {
+                HIPCHK(c, launch_stage_direct<T>(c->stream, cb, ex, phys<T>(c), (T*)c->F[k]));
+            }
+        } else if (pl.extrap) {
             if (formed[k]) {
                 cb = plain<T>(mkbuf(k));
             } else if (cb.nf > 0) {
@@ -802,7 +846,23 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
         if (c->rec)
             c->rec_unsupported = true;
         else
-            HIPCHK(c, launch_reduce_max(c->stream, c->parts, nred, c->scal));
+            HIPCHK(c, launch_reduce_max(c->stream, c->parts, nred, c->err_dev));
+    }
+    return LLGX_OK;
+}
+
+// The slot the error norm of adaptive attempts is written to: pinned host
+// memory, so an attempt ends with the reduction and one wait (a copy of the
+// value to pageable memory cost a launch and a staging pass more)
+static llgx_status host_slot(Ctx* c) {
+    if (c->err_host) return LLGX_OK;
+    void* host = nullptr;
+    HIPCHK(c, hipHostMalloc(&host, sizeof(double), hipHostMallocMapped));
+    const hipError_t e = hipHostGetDevicePointer((void**)&c->err_dev, host, 0);
+    if (e != hipSuccess) {
+        (void)hipHostFree(host);
+        return c->fail(LLGX_E_HIP, "no device address of pinned memory: %s", hipGetErrorString(e));
+    c->err_host = (double*)host;
     }
     return LLGX_OK;
 }
@@ -843,6 +903,15 @@ static llgx_status check_stepper(Ctx* c, const llgx_stepper* s, const Tableau** 
     if (s->adaptive && (*tab)->order_hat == 0) return c->fail(LLGX_E_ARG, "%s has no embedded estimate", (*tab)->name);
     if (!(s->h > 0)) return c->fail(LLGX_E_ARG, "h must be > 0");
     if (!c->have_kernel) return c->fail(LLGX_E_STATE, "demag kernel not computed (llgx_precompute_demag)");
+    if (c->empty_stale) {
+        // before any launch or capture of the step
+        llgx_status st = detect_empty(c);
+        if (st) return st;
+    }
+    if (s->adaptive) {
+        llgx_status st = host_slot(c);
+        if (st) return st;
+    }
     if (!c->have_m) return c->fail(LLGX_E_STATE, "magnetization not set (llgx_set_m)");
     if (s->method != c->cur_method || *p != c->cur_p) {
         c->hist.clear();
@@ -917,7 +986,8 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             pr.coef[1] = (T)(-0.5 * h * r);
             pr.nf = 2;
         }
-        {
+        const bool direct = extrap && stage_direct_ok(c->ncell * c->nb, sizeof(T), pr.nf);
+        if (!direct) {
             PROF(LLGX_K_COMBINE);
             HIPCHK(c, launch_combine<T>(c->stream, 3 * c->ncell * c->nb, pr, (T*)c->Mk));
         }
@@ -926,6 +996,17 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             ex.n = 1;
             ex.w[0] = T(1);
             if (p == 0) {
+            } else if (direct) {
+                std::vector<double> nodes;
+                for (int i = 0; i < p; ++i) {
+                    nodes.push_back(c->hist[i].t - c->t);
+                    ex.g[i] = (const T*)c->G[c->hist[i].slot];
+                }
+                nodes.push_back(0.0);
+                ex.g[p] = (const T*)c->G[c->abm_slot];
+                const std::vector<double> w = lagrange(nodes, h);
+                for (int i = 0; i <= p; ++i) ex.w[i] = (T)w[i];
+                ex.n = p + 1;
                 ex.g[0] = (const T*)c->G[c->abm_slot];
             } else {
                 std::vector<double> nodes;
@@ -948,8 +1029,11 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
                 ex.g[0] = (const T*)c->E[0];
             }
             PROF(LLGX_K_EXTRAP);
-            HIPCHK(c, launch_extrap_rhs<T>(c->stream, plain<T>(c->Mk), ex, phys<T>(c), (T*)c->F[1],
-                                           NextStage<T>{nullptr, nullptr, T(0)}));
+            if (direct)
+                HIPCHK(c, launch_stage_direct<T>(c->stream, pr, ex, phys<T>(c), (T*)c->F[1]));
+            else
+                HIPCHK(c, launch_extrap_rhs<T>(c->stream, plain<T>(c->Mk), ex, phys<T>(c), (T*)c->F[1],
+                                               NextStage<T>{nullptr, nullptr, T(0)}));
             c->n_extrap++;
         } else {
             XinvOut out{nullptr, c->F[1], nullptr, nullptr, 0.0};
@@ -982,9 +1066,9 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
         if (!s->adaptive) break;
         {
             PROF(LLGX_K_OTHER);
-            HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->scal));
+            HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->err_dev));
         }
-        HIPCHK(c, hipMemcpyAsync(&err, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        err = *(volatile double*)c->err_host;
         HIPCHK(c, hipStreamSynchronize(c->stream));
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
@@ -1079,7 +1163,7 @@ static llgx_status do_step(Ctx* c, const llgx_stepper* s, llgx_step_info* info) 
         else
             c->n_exact += later;
         if (!s->adaptive) break;
-        HIPCHK(c, hipMemcpyAsync(&err, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        err = *(volatile double*)c->err_host;
         HIPCHK(c, hipStreamSynchronize(c->stream));
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
@@ -1336,6 +1420,7 @@ static void release(Ctx* c) {
     for (int i = 0; i < MAX_HIST; ++i)
         if (c->G[i]) (void)hipFree(c->G[i]);
     for (int i = 0; i < MAX_F; ++i)
+    if (c->err_host) (void)hipHostFree(c->err_host);
         if (c->E[i] && !c->e_in_b[i]) (void)hipFree(c->E[i]);
     for (auto& kv : c->tw_work) (void)hipFree(kv.second);
     for (auto& kv : c->tw_f64) (void)hipFree(kv.second);
@@ -1865,11 +1950,6 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
                 c->n_extrap += tab->S - 1;
             else
                 c->n_exact += tab->S - 1;
-            if (s->adaptive &&
-                hipMemcpyAsync(&errs[g], c->scal, sizeof(double), hipMemcpyDeviceToHost, c->stream) != hipSuccess) {
-                bt->err = "error-norm copy failed";
-                return LLGX_E_HIP;
-            }
         }
         if (!s->adaptive) break;
         if (hipStreamSynchronize(bt->stream) != hipSuccess) {
@@ -1918,6 +1998,7 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
         info->h_next = c0->h_next;
         info->err = err;
         info->rejected = rejected;
+        for (size_t g = 0; g < ng; ++g) errs[g] = *(volatile double*)bt->groups[g]->err_host;
         info->exact_evals = (int)(c0->n_exact - ex0);
         info->extrap_evals = (int)(c0->n_extrap - xt0);
         info->forced = forced;

@@ -1,0 +1,60 @@
+"""Sub-steps in one launch (stage input and Eq. (6) field formed inside) against
+the separate combination, Eq. (6) and stage launches: job-table steps of a batch
+keep the separate ones, forked-stream steps take the single launch on these
+meshes, and the two must agree bit for bit for every tableau, order and number of
+terms, with empty cells and with rows that end inside a block."""
+
+import numpy as np
+import pytest
+
+import workloads
+from tests.gpu_util import film, log, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+CELL = (4e-9, 4e-9, 3e-9)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("method,p", [("RK23", 0), ("RK23", 3), ("RKF45", 1), ("RKCK45", 4), ("RKDP54", 5),
+                                      ("RKF56", 2), ("HEUN", 2)])
+def test_direct_equals_separate(method, p, prec):
+    import torch
+
+    import paper_2107_06729_amd as llgx
+    log(f"direct {method} {p} {prec}")
+    meshes = [(21, 13, 3), (70, 9, 1)]
+    stream = torch.cuda.Stream()
+    got = []
+    for launch in ("jobs", "streams"):
+        bt = llgx.Batch([film(n, CELL, K=2e4, Ha=(h, 1e3, 0.0)) for n in meshes for h in (1e4, -2e4)], prec, stream=stream)
+        bt.set_launch(launch)
+        bt.precompute_demag()
+        with torch.cuda.stream(stream):
+            for i in range(4):
+                n = meshes[i // 2]
+                M = workloads.random_m(n, 8e5, 90 + i)
+                if i % 2:
+                    M = workloads.masked(M, workloads.checkerboard_mask(n, 4))
+                bt.set_m(i, to_dev(M, prec))
+        bt.run_fixed(llgx.make_stepper(method, extrap=p, h=1e-14), p + 4, use_graph=True)
+        assert bt.info()["job_table"] == (launch == "jobs"), bt.last_error()
+        got.append([to_host(bt.get_m(i)) for i in range(4)])
+        bt.close()
+    for a, b in zip(*got):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("op", ["heff", "rhs"])
+def test_field_call_finds_empty_cells_itself(op):
+    """A field call tests every neighbour; the same M held as a handle's state
+    does so because its flag is set, and a full mesh takes the same values as one
+    whose only empty cell is elsewhere."""
+    from tests.gpu_util import sim
+    n = (20, 12, 2)
+    M = workloads.random_m(n, 8e5, 95)
+    s = sim(film(n, CELL), "f64")
+    full = to_host(getattr(s, op)(to_dev(M, "f64")))
+    s.set_m(to_dev(workloads.masked(M, workloads.checkerboard_mask(n, 4)), "f64"))
+    # the state's flag does not reach a field call
+    assert np.array_equal(to_host(getattr(s, op)(to_dev(M, "f64"))), full)
