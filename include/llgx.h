@@ -175,8 +175,8 @@ llgx_status llgx_rhs(llgx_handle h, const void* M_dev, void* F_dev);
  * For callers that cannot allocate device memory: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.
  * llgx_demag_noalloc computes exactly what llgx_demag computes (the same
- * kernels and launch variants, so the same bits), but its FFT spectra and
- * its empty-cell flag live in a static device array of the library of
+ * kernels and launch variants, so the same bits), but its FFT spectra live
+ * in a static device array of the library of
  * LLGX_NOALLOC_SCRATCH_BYTES, one per GPU the library runs on, held until
  * the process ends (not in the handle's workspace).  The call allocates and
  * frees nothing, issues no hipMemset, and enqueues kernels only.
@@ -189,9 +189,8 @@ llgx_status llgx_rhs(llgx_handle h, const void* M_dev, void* F_dev);
  *   80.2 MB.  A larger mesh gives LLGX_E_ARG and enqueues nothing.
  * Every call on one GPU uses that GPU's one array: calls whose work overlaps
  * on a GPU (other streams, other host threads) race and must be ordered by
- * the caller.  The array keeps the last call's contents; the flag is cleared
- * by a kernel at every call and the spectra are fully rewritten before they
- * are read (their padding columns, never read into a result, are left).
+ * the caller.  The array keeps the last call's contents; the spectra are
+ * fully rewritten before they are read (their padding columns, never read into a result, are left).
  * Errors as llgx_demag (LLGX_E_STATE before llgx_precompute_demag). */
 #define LLGX_NOALLOC_SCRATCH_BYTES (128u << 20)
 llgx_status llgx_demag_noalloc(llgx_handle h, const void* M_dev, void* H_dev);

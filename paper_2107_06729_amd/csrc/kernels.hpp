@@ -99,7 +99,7 @@ struct Phys {
     T gpa;             // gamma alpha / ((1 + alpha^2) Ms)
     T n00[3];          // self term of Eq. (6)
     const T* hab;      // applied field of each sample [nb][3] (device)
-    const int* empty;  // device flag: nonzero when some cell has M = 0 (no material)
+    const int* empty;  // device flag: nonzero when some cell has M = 0 (no material), or nobody looked
     int nx, ny, nz;
     int nb;            // samples of this mesh processed by one launch
 };

@@ -294,7 +294,7 @@ static Phys<T> phys(const Ctx* c) {
     ph.nz = c->nz;
     ph.nb = c->nb;
     ph.hab = (const T*)c->hab;
-    ph.empty = c->empty_use ? c->empty_use : c->empty_flag + (c->field_input ? 1 : 0);
+    ph.empty = c->empty_flag + (c->field_input ? 1 : 0);
     return ph;
 }
 
@@ -306,16 +306,15 @@ static Combo<T> plain(const void* base) {
     return cb;
 }
 
-// Recompute an empty-cell flag (slot 0: from the state M; slot 1: from the
-// input of a field call) on the stream, with no host synchronisation.
-static llgx_status detect_empty(Ctx* c, const void* M = nullptr, int slot = 0) {
-    int* flag = c->empty_flag + slot;
-    if (!M) M = c->M;
-    HIPCHK(c, hipMemsetAsync(flag, 0, sizeof(int), c->stream));
+// Recompute the empty-cell flag of the state M on the stream, with no host
+// synchronisation.
+static llgx_status detect_empty(Ctx* c) {
+    HIPCHK(c, launch_fill_int(c->stream, c->empty_flag, 1, 0));
     if (c->prec == LLGX_F32)
-        HIPCHK(c, launch_detect_empty<float>(c->stream, c->ncell, c->nb, (const float*)M, flag));
+        HIPCHK(c, launch_detect_empty<float>(c->stream, c->ncell, c->nb, (const float*)c->M, c->empty_flag));
     else
-        HIPCHK(c, launch_detect_empty<double>(c->stream, c->ncell, c->nb, (const double*)M, flag));
+        HIPCHK(c, launch_detect_empty<double>(c->stream, c->ncell, c->nb, (const double*)c->M, c->empty_flag));
+    c->empty_stale = false;
     return LLGX_OK;
 }
 
@@ -668,6 +667,7 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     std::vector<double> times;
     std::vector<int> field_of(tab->S, -1);
     bool fuse_ep = false;
+    EPoly<T> ep_fused{};
     // sub-steps in one launch each, unless the stage inputs are all chained and
     // the first sub-step forms the Eq. (6) fields (RK4: as few launches already)
     int terms = 0;  // most terms of a stage input that is not chained
@@ -678,7 +678,6 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     }
     const bool direct = pl.extrap && !c->rec && (terms > 0 || tab->S < 3) &&
                         stage_direct_ok(c->ncell * c->nb, sizeof(T), terms);
-    EPoly<T> ep_fused{};
     if (pl.extrap) {
         for (auto& hh : c->hist) {
             nodes.push_back(hh.t - c->t);
@@ -862,8 +861,8 @@ static llgx_status host_slot(Ctx* c) {
     if (e != hipSuccess) {
         (void)hipHostFree(host);
         return c->fail(LLGX_E_HIP, "no device address of pinned memory: %s", hipGetErrorString(e));
-    c->err_host = (double*)host;
     }
+    c->err_host = (double*)host;
     return LLGX_OK;
 }
 
@@ -903,6 +902,7 @@ static llgx_status check_stepper(Ctx* c, const llgx_stepper* s, const Tableau** 
     if (s->adaptive && (*tab)->order_hat == 0) return c->fail(LLGX_E_ARG, "%s has no embedded estimate", (*tab)->name);
     if (!(s->h > 0)) return c->fail(LLGX_E_ARG, "h must be > 0");
     if (!c->have_kernel) return c->fail(LLGX_E_STATE, "demag kernel not computed (llgx_precompute_demag)");
+    if (!c->have_m) return c->fail(LLGX_E_STATE, "magnetization not set (llgx_set_m)");
     if (c->empty_stale) {
         // before any launch or capture of the step
         llgx_status st = detect_empty(c);
@@ -912,7 +912,6 @@ static llgx_status check_stepper(Ctx* c, const llgx_stepper* s, const Tableau** 
         llgx_status st = host_slot(c);
         if (st) return st;
     }
-    if (!c->have_m) return c->fail(LLGX_E_STATE, "magnetization not set (llgx_set_m)");
     if (s->method != c->cur_method || *p != c->cur_p) {
         c->hist.clear();
         c->fsal_valid = false;
@@ -996,6 +995,7 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             ex.n = 1;
             ex.w[0] = T(1);
             if (p == 0) {
+                ex.g[0] = (const T*)c->G[c->abm_slot];
             } else if (direct) {
                 std::vector<double> nodes;
                 for (int i = 0; i < p; ++i) {
@@ -1007,7 +1007,6 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
                 const std::vector<double> w = lagrange(nodes, h);
                 for (int i = 0; i <= p; ++i) ex.w[i] = (T)w[i];
                 ex.n = p + 1;
-                ex.g[0] = (const T*)c->G[c->abm_slot];
             } else {
                 std::vector<double> nodes;
                 EPoly<T> ep{};
@@ -1068,8 +1067,8 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             PROF(LLGX_K_OTHER);
             HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->err_dev));
         }
-        err = *(volatile double*)c->err_host;
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        err = *(volatile double*)c->err_host;
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
             err <= 0.0 ? s->c_max : std::min(std::max(std::pow(0.8 * s->e_max / err, 1.0 / 3.0), s->c_min), s->c_max);
@@ -1163,8 +1162,8 @@ static llgx_status do_step(Ctx* c, const llgx_stepper* s, llgx_step_info* info) 
         else
             c->n_exact += later;
         if (!s->adaptive) break;
-        err = *(volatile double*)c->err_host;
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        err = *(volatile double*)c->err_host;
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
             err <= 0.0 ? s->c_max
@@ -1420,8 +1419,8 @@ static void release(Ctx* c) {
     for (int i = 0; i < MAX_HIST; ++i)
         if (c->G[i]) (void)hipFree(c->G[i]);
     for (int i = 0; i < MAX_F; ++i)
-    if (c->err_host) (void)hipHostFree(c->err_host);
         if (c->E[i] && !c->e_in_b[i]) (void)hipFree(c->E[i]);
+    if (c->err_host) (void)hipHostFree(c->err_host);
     for (auto& kv : c->tw_work) (void)hipFree(kv.second);
     for (auto& kv : c->tw_f64) (void)hipFree(kv.second);
 }
@@ -1666,7 +1665,9 @@ static llgx_status create_ctx(const llgx_problem* p, int nb, const double* ha_li
         if (hipMemset(c->specA, 0, bytesA) != hipSuccess) st = c->fail(LLGX_E_HIP, "hipMemset failed");
         if (st == LLGX_OK && c->specB && hipMemset(c->specB, 0, bytesB) != hipSuccess)
             st = c->fail(LLGX_E_HIP, "hipMemset failed");
-        if (st == LLGX_OK && hipMemset(c->empty_flag, 0, 16) != hipSuccess) st = c->fail(LLGX_E_HIP, "hipMemset failed");
+        const int flags[4] = {0, 1, 0, 0};
+        if (st == LLGX_OK && hipMemcpy(c->empty_flag, flags, sizeof flags, hipMemcpyHostToDevice) != hipSuccess)
+            st = c->fail(LLGX_E_HIP, "hipMemcpy of the empty-cell flags failed");
     }
     if (st == LLGX_OK) {
         // each sample's applied field (the problem's own when no list is given)
@@ -1997,8 +1998,8 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
         info->h_used = h;
         info->h_next = c0->h_next;
         info->err = err;
-        info->rejected = rejected;
         for (size_t g = 0; g < ng; ++g) errs[g] = *(volatile double*)bt->groups[g]->err_host;
+        info->rejected = rejected;
         info->exact_evals = (int)(c0->n_exact - ex0);
         info->extrap_evals = (int)(c0->n_extrap - xt0);
         info->forced = forced;
@@ -2254,10 +2255,7 @@ static llgx_status batch_copy(llgx_batch b, int32_t i, const void* src, void* ds
         c->fsal_valid = false;
         c->abm_have_f = c->abm_have_prev = false;
         c->have_m = true;
-        if (e == hipSuccess && detect_empty(c) != LLGX_OK) {
-            bt->err = c->err;
-            return LLGX_E_HIP;
-        }
+        c->empty_stale = true;  // one look at the whole group before its next step
     } else {
         e = hipMemcpyAsync(dst_or_null, base, bytes, hipMemcpyDeviceToDevice, c->stream);
     }
@@ -2436,8 +2434,7 @@ static llgx_status field_call(llgx_handle h, const void* M_dev, void* out_dev, i
         out.f = out_dev;
     else
         out.h = out_dev;
-    llgx_status st = detect_empty(c, M_dev, 1);
-    if (st) return st;
+    llgx_status st;
     c->field_input = true;
     if (c->prec == LLGX_F32)
         st = eval_exact<float>(c, plain<float>(M_dev), nullptr, mode, (const float*)M_dev, out);
@@ -2457,7 +2454,7 @@ llgx_status llgx_demag_noalloc(llgx_handle h, const void* M_dev, void* H_dev) {
     if (!M_dev || !H_dev) return c->fail(LLGX_E_ARG, "null pointer");
     if (!c->have_kernel) return c->fail(LLGX_E_STATE, "demag kernel not computed (llgx_precompute_demag)");
     if (!c->noalloc) return c->fail(LLGX_E_STATE, "no scratch address on this device");
-    // layout: [0, 256) the empty-cell flag, then spectrum A, then spectrum B
+    // layout: 256 bytes unused, then spectrum A, then spectrum B
     const size_t cbytes = c->spectral == LLGX_SPEC_NATIVE ? 2 * c->tsz : 4;
     const size_t bytesA = 3 * (size_t)c->nz * c->ny * c->SX * cbytes * c->nb;
     const size_t bytesB = c->Py > 1 ? 3 * (size_t)c->nz * c->Py * c->SX * cbytes * c->nb : 0;
@@ -2473,20 +2470,14 @@ llgx_status llgx_demag_noalloc(llgx_handle h, const void* M_dev, void* H_dev) {
         return c->fail(LLGX_E_ARG, "mesh needs %zu bytes of scratch; llgx_demag_noalloc has %zu", need,
                        (size_t)LLGX_NOALLOC_SCRATCH_BYTES);
     char* base = (char*)c->noalloc;
-    int* flag = (int*)base;
-    HIPCHK(c, launch_fill_int(c->stream, flag, 1, 0));
-    if (c->prec == LLGX_F32)
-        HIPCHK(c, launch_detect_empty<float>(c->stream, c->ncell, c->nb, (const float*)M_dev, flag));
-    else
-        HIPCHK(c, launch_detect_empty<double>(c->stream, c->ncell, c->nb, (const double*)M_dev, flag));
-    c->empty_use = flag;
+    c->field_input = true;  // (the demagnetizing field alone tests no neighbour)
     c->spec_use[0] = base + offA;
     c->spec_use[1] = bytesB ? base + offB : nullptr;
     XinvOut out{H_dev, nullptr, nullptr};
     llgx_status st = c->prec == LLGX_F32
                          ? eval_exact<float>(c, plain<float>(M_dev), nullptr, XINV_DEMAG, (const float*)M_dev, out)
                          : eval_exact<double>(c, plain<double>(M_dev), nullptr, XINV_DEMAG, (const double*)M_dev, out);
-    c->empty_use = nullptr;
+    c->field_input = false;
     c->spec_use[0] = c->spec_use[1] = nullptr;
     return st;
 }
