@@ -244,7 +244,8 @@ llgx_status llgx_profile_read(llgx_handle h, double ms[LLGX_K_COUNT], int64_t la
  * Each FFT pass of an exact evaluation (kinds LLGX_K_XFWD .. LLGX_K_XINV
  * above, indices 0..4 of the arrays below) can be launched in a few variants
  * -- tile widths and rows per workgroup -- that give bit-identical results
- * and differ only in speed.  Variant 0 is the default.
+ * and differ only in speed.  A new handle starts with a choice by lengths and
+ * sizes.
  *
  * llgx_autotune: times every variant of every pass (reps back-to-back
  * launches each, between HIP events on the handle's stream, in three rounds

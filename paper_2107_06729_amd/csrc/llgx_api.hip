@@ -1488,6 +1488,46 @@ static std::string tune_key(const Ctx* c) {
     return b;
 }
 
+// Variants a handle starts with (the tuner's choice for its key replaces them).
+// Every choice gives the same bits; the lines lie where the tiles of variant 0
+// (the widest that fill a workgroup) lost, microseconds per pass of variant 0
+// against the one chosen:
+//   x forward, FP32: 4 or 8 rows a tile up to LX = 256 (64x64x1 3.7 / 3.3,
+//     128x128x32 7.6 / 6.9, 256x256x16 10.9 / 10.8); longer rows only where that
+//     leaves fewer than 768 tiles (512x512x1 6.5 / 5.9; 300x300x20 18.6 / 22.6 the
+//     other way).  FP64: half tiles below 512 of them (256x64x1 4.7 / 4.3; 200x120x10
+//     8.6 / 9.7 the other way), double ones from LX = 320 on, whose rows were rounded
+//     down to a power of two (300x130x9 15.2 / 12.3, 512x512x64 405 / 293).
+//   x inverse: half tiles in FP32 (256x64x1 7.0 / 4.8, 256x256x16 14.2 / 12.7, BF16
+//     512x512x64 284 / 222; FP32 512x512x64 224 / 233 the other way); FP64 below 1024
+//     tiles (200x120x10 10.4 / 9.2; 128x128x32 13.2 / 14.0 the other way).
+//   y passes, spectra in the working precision: half-width tiles for FP32 lengths
+//     320 to 512 (256x256x16 16.5 / 14.9, 15.2 / 13.8; 256: level), FP64 256 to 512
+//     (300x130x9 27.4 / 15.6, 256x256x16 26.5 / 24.6); 16-bit rows of half a
+//     line lose (15.2 / 16.3).
+//   z pass: double tiles up to length 8 and at 24 (600x520x4 36.3 / 30.0, 300x300x12
+//     28.8 / 27.1), FP64 up to 16 (400x400x6 85.9 / 68.7); half ones for FP64 64
+//     (128x128x32 27.3 / 24.5).  The fused pass of thin meshes keeps its variant 0.
+static void default_variants(Ctx* c) {
+    const bool f32 = c->prec == LLGX_F32, native = c->spectral == LLGX_SPEC_NATIVE;
+    const long rows = 3L * c->ny * c->nz * c->nb, mesh_rows = (long)c->ny * c->nz * c->nb;
+    // rows of a variant-0 tile of the x passes
+    auto tile_rows = [&](int elems, int most) {
+        int r = 1;
+        while (2 * r * std::max(c->LX, 1) <= elems && 2 * r <= most) r *= 2;
+        return r;
+    };
+    const long xf = rows / tile_rows(f32 ? 2048 : 1024, 16), xi = mesh_rows / tile_rows(f32 ? 1024 : 512, 8);
+    if (f32)
+        c->var[LLGX_K_XFWD] = c->LX <= 256 || xf < 768 ? 1 : 0;
+    else
+        c->var[LLGX_K_XFWD] = c->LX >= 320 ? 2 : xf < 512 ? 1 : 0;
+    c->var[LLGX_K_XINV] = f32 || xi < 1024 ? 1 : 0;
+    const int ylow = f32 ? 320 : 256;
+    c->var[LLGX_K_YFWD] = c->var[LLGX_K_YINV] = native && c->Py >= ylow && c->Py <= 512 ? 1 : 0;
+    if (!c->thin) c->var[LLGX_K_ZMUL] = c->Pz <= 8 || c->Pz == 24 || (!f32 && c->Pz == 16) ? 2 : !f32 && c->Pz == 64 ? 1 : 0;
+}
+
 static void drop_graphs(Ctx* c) {
     for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     c->graphs.clear();
@@ -1701,6 +1741,7 @@ static llgx_status create_ctx(const llgx_problem* p, int nb, const double* ha_li
         delete c;
         return st;
     }
+    default_variants(c);
     apply_tuned(c);
     *out = c;
     return LLGX_OK;
@@ -1957,6 +1998,7 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
             bt->err = "synchronisation failed";
             return LLGX_E_HIP;
         }
+        for (size_t g = 0; g < ng; ++g) errs[g] = *(volatile double*)bt->groups[g]->err_host;
         err = 0.0;
         for (double e : errs) err = std::isfinite(e) && std::isfinite(err) ? std::max(err, e) : NAN;
         if (!std::isfinite(err)) {
@@ -1998,7 +2040,6 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
         info->h_used = h;
         info->h_next = c0->h_next;
         info->err = err;
-        for (size_t g = 0; g < ng; ++g) errs[g] = *(volatile double*)bt->groups[g]->err_host;
         info->rejected = rejected;
         info->exact_evals = (int)(c0->n_exact - ex0);
         info->extrap_evals = (int)(c0->n_extrap - xt0);
