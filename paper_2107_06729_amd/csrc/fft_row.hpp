@@ -1,8 +1,17 @@
 // FFTs along contiguous rows held in LDS, for the x passes.
 //
-// NR rows of length L; element i of row r lives at buf[r * RS + P(i)] with
-// P(i) = i + i / 8: one padding element after every 8, so the stride-R0
-// writes of the first stage spread over the banks.  The stage
+// NR rows of length L; element i of row r lives at buf[r * RS + P(i)].  Powers
+// of two have P(i) = i + i / 16 (FP64: i / 8): the LDS serves 128 bytes a cycle,
+// 16 complex values (8), so runs of consecutive elements, two thirds of the
+// accesses, stay free of conflicts, and the stride-8 writes of the first stage
+// spread over the banks.  (One padding element after every 8 FP32 values made
+// every run take two rounds: 256x1000x4, 43 % of the LDS cycles of the fused
+// pass.)  Other lengths are not padded (their R0 is a multiple of 3 or 5: at
+// most a few lanes share a bank, in that stage alone, and the padded index of
+// every element cost more: a third of the instructions of a 640-row tile were
+// index arithmetic).  The stages address element x0 + r S of a unit as P(x0) +
+// dP(r S), one index per unit: exact when S is a multiple of the padding step, or
+// when S divides it and x0 mod S + r S crosses no step that r S does not.  The stage
 // schedule is that of fft_lds.hpp (radix R0, then radix 8).
 //
 // Work unit of every stage: one butterfly j of one row, j fastest, so
@@ -27,13 +36,17 @@ struct RowFFT {
     using C = cx<T>;
     static constexpr int R0 = first_radix(L);
     static constexpr int NSTAGE = fft_stages(L, R0);
-    static constexpr int RS = L + L / 8 + 1;  // padded row stride (complex)
+    static constexpr bool PAD = (L & (L - 1)) == 0;
+    static constexpr int PS = sizeof(T) == 4 ? 4 : 3;          // a padding element after 2^PS
+    static constexpr int RS = L + (PAD ? L >> PS : 0) + 1;  // row stride (complex)
     static constexpr int LDS_ELEMS = NR * RS;
     static constexpr int NU0 = NR * (L / R0), U0 = (NU0 + NT - 1) / NT;
     static constexpr int NU8 = NR * (L / 8), U8 = (NU8 + NT - 1) / NT;
     static_assert(L >= 2, "length");
 
-    static __device__ __forceinline__ int P(int i) { return i + (i >> 3); }
+    static __device__ __forceinline__ int P(int i) { return PAD ? i + (i >> PS) : i; }
+    // P(x0 + d) - P(x0) for the strides of the stages
+    static constexpr int dP(int d) { return PAD ? d + (d >> PS) : d; }
 
     // unit u of a stage with L/R butterflies per row
     template <int R>
@@ -64,9 +77,9 @@ struct RowFFT {
                     for (int q = (R0 + 1) / 2; q < R0; ++q) x[m][q] = C{T(0), T(0)};
                 }
                 dft_r<R0, INV>(x[m]);
-                C* rb = buf + row * RS;
+                C* rb = buf + row * RS + P(j * R0);
 #pragma unroll
-                for (int q = 0; q < R0; ++q) rb[P(j * R0 + q)] = x[m][q];
+                for (int q = 0; q < R0; ++q) rb[dP(q)] = x[m][q];
             }
         }
     }
@@ -81,10 +94,10 @@ struct RowFFT {
                 int row, j;
                 unit<8>(u, row, j);
                 const int k = j % NS;
-                const C* rb = buf + row * RS;
+                const C* rb = buf + row * RS + P(j);
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    const C a = rb[P(j + r * (L / 8))];
+                    const C a = rb[dP(r * (L / 8))];
                     const C w = tw[r * k * (L / (NS * 8))];
                     x[m][r] = r == 0 ? a : (INV ? cmulc(a, w) : cmul(a, w));
                 }
@@ -99,10 +112,9 @@ struct RowFFT {
                 int row, j;
                 unit<8>(u, row, j);
                 const int k = j % NS;
-                const int base = (j / NS) * NS * 8 + k;
-                C* rb = buf + row * RS;
+                C* rb = buf + row * RS + P((j / NS) * NS * 8 + k);
 #pragma unroll
-                for (int r = 0; r < 8; ++r) rb[P(base + r * NS)] = x[m][r];
+                for (int r = 0; r < 8; ++r) rb[dP(r * NS)] = x[m][r];
             }
         }
         __syncthreads();
@@ -130,9 +142,9 @@ struct RowFFT {
             if (live0(u)) {
                 int row, j;
                 unit<R0>(u, row, j);
-                const C* rb = buf + row * RS;
+                const C* rb = buf + row * RS + P(j);
 #pragma unroll
-                for (int q = 0; q < R0; ++q) x[m][q] = rb[P(j + q * (L / R0))];
+                for (int q = 0; q < R0; ++q) x[m][q] = rb[dP(q * (L / R0))];
             }
         }
         __syncthreads();
@@ -140,12 +152,12 @@ struct RowFFT {
         __syncthreads();
     }
 
-    // outputs x[8] of the last stage (elements j + r L/8) of one unit
+    // outputs x[8] of the last stage (elements j + r L/8) of one unit, rb at P(j)
     static __device__ __forceinline__ void last_regs(const C* rb, const C* __restrict__ tw, int j, C (&x)[8]) {
         constexpr int NS = L / 8;
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            const C a = rb[P(j + r * NS)];
+            const C a = rb[dP(r * NS)];
             const C w = tw[r * j];
             x[r] = r == 0 ? a : (INV ? cmulc(a, w) : cmul(a, w));
         }
@@ -162,7 +174,7 @@ struct RowFFT {
                 int row, j;
                 unit<8>(u, row, j);
                 C x[8];
-                last_regs(buf + row * RS, tw, j, x);
+                last_regs(buf + row * RS + P(j), tw, j, x);
 #pragma unroll
                 for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) f(row, j + r * (L / 8), x[r]);
             }
@@ -180,11 +192,11 @@ struct RowFFT {
                 if (NU8 % NT == 0 || u < NU8) {
                     int row, j;
                     unit<8>(u, row, j);
-                    C* rb = buf + row * RS;
+                    C* rb = buf + row * RS + P(j);
                     C x[8];
                     last_regs(rb, tw, j, x);
 #pragma unroll
-                    for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) rb[P(j + r * (L / 8))] = x[r];
+                    for (int r = 0; r < (HALF_OUT ? 4 : 8); ++r) rb[dP(r * (L / 8))] = x[r];
                 }
             }
             __syncthreads();

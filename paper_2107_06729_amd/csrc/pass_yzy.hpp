@@ -48,7 +48,7 @@ struct YzyShared {
 // LDS bytes of a tile (for the host's choice of the path)
 template <typename T>
 constexpr long yzy_lds(int LY, int nz, int tk) {
-    return (3L * nz * tk * (LY + LY / 8 + 1) + LY) * 2 * (long)sizeof(T);
+    return (3L * nz * tk * (LY + ((LY & (LY - 1)) == 0 ? LY / (sizeof(T) == 4 ? 16 : 8) : 0) + 1) + LY) * 2 * (long)sizeof(T);
 }
 constexpr long YZY_LDS_MAX = 128 * 1024;
 
