@@ -156,6 +156,7 @@ __device__ __forceinline__ NextStage<T> ld(const NextStage<T>* p) {
     n.m0 = gload(&p->m0);
     n.mnext = gload(&p->mnext);
     n.cnext = sload(&p->cnext);
+    n.nf = 0;  // job-table stages form chained inputs only
     return n;
 }
 

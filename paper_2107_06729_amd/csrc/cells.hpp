@@ -222,35 +222,74 @@ __device__ __forceinline__ void stage_rhs_g(const Combo<T>& mk, const T g[3], T 
     llg_at(m, H, ph, f);
 }
 
-// the same with g read from the stored or Eq. (6) field ex.g[0]
-template <typename T>
+// the same with g from ex: NG = 1 the stored or Eq. (6) field ex.g[0]; else Eq.
+// (6) at the stage's own time, summed here from at most NG stored fields (loads
+// past ex.n read node 0 and are left out of the sum; the sums of epoly_*, term
+// for term)
+template <typename T, int NG = 1>
 __device__ __forceinline__ void stage_rhs(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
                                           const CellIdx& ci, long N, T m[3], T f[3]) {
+    const long i0 = ci.off + ci.cell;
     T g[3];
+    if constexpr (NG == 1) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) g[c] = ex.g[0][ci.off + c * N + ci.cell];
-    stage_rhs_g<T>(mk, g, ex.w[0], ph, ci, N, m, f);
+        for (int c = 0; c < 3; ++c) g[c] = ex.g[0][i0 + c * N];
+        stage_rhs_g<T>(mk, g, ex.w[0], ph, ci, N, m, f);
+    } else {
+        T gk[NG][3];
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const T* p = ex.g[i < ex.n ? i : 0];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) gk[i][c] = p[i0 + c * N];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            g[c] = T(0);
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const T v = g[c] + ex.w[i] * gk[i][c];
+                g[c] = i < ex.n ? v : g[c];
+            }
+        }
+        stage_rhs_g<T>(mk, g, T(1), ph, ci, N, m, f);
+    }
 }
 
-template <typename T>
+// Sub-step F and, when nx.mnext is set, the next stage input of Eq. (4): its NX
+// terms of earlier stages are read at the cell (with M0), its own term comes
+// from registers, so no combination pass reads F back
+template <typename T, int NX = 0, int NG = 1>
 __device__ __forceinline__ void stage_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
                                             T* __restrict__ F, const NextStage<T>& nx, const CellBlk& k) {
     const long N = (long)ph.nx * ph.ny * ph.nz;
     const CellIdx ci = cell_index(ph, k);
     if (!ci.ok) return;
-    // M0 of the chained output is loaded with the stencil, not after it
+    const long i0 = ci.off + ci.cell;
+    // M0 and the terms of the next input are loaded with the stencil, not after it
     T m0[3] = {T(0), T(0), T(0)};
+    T t[NX > 0 ? NX : 1][3];
     if (nx.mnext) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) m0[c] = nx.m0[ci.off + c * N + ci.cell];
+        for (int c = 0; c < 3; ++c) m0[c] = nx.m0[i0 + c * N];
+#pragma unroll
+        for (int l = 0; l < NX; ++l)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) t[l][c] = nx.f[l][i0 + c * N];
     }
     T m[3], f[3];
-    stage_rhs<T>(mk, ex, ph, ci, N, m, f);
+    stage_rhs<T, NG>(mk, ex, ph, ci, N, m, f);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) F[ci.off + c * N + ci.cell] = f[c];
+    for (int c = 0; c < 3; ++c) F[i0 + c * N] = f[c];
     if (nx.mnext) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) nx.mnext[ci.off + c * N + ci.cell] = m0[c] + nx.cnext * f[c];
+        for (int c = 0; c < 3; ++c) {
+            T v = m0[c];
+#pragma unroll
+            for (int l = 0; l < NX; ++l) v += nx.coef[l] * t[l][c];
+            const T own = v + nx.cnext * f[c];
+            nx.mnext[i0 + c * N] = nx.cnext != T(0) ? own : v;
+        }
     }
 }
 
@@ -307,7 +346,7 @@ __device__ __forceinline__ void stage_ep_block(const Combo<T>& mk, const Extrap<
 // stage's own F_S, which is taken from registers and never stored.  mnew may
 // be M0 itself (fixed steps): each cell's M0 is read before its update is
 // written, and no other cell's update reads it.
-template <typename T, int NF>
+template <typename T, int NF, int NG = 1>
 __device__ __forceinline__ void stage_final_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
                                                   const T* M0, const Final<T>& fs, double inv_ms, T* mnew,
                                                   double* __restrict__ parts, const CellBlk& k) {
@@ -325,7 +364,7 @@ __device__ __forceinline__ void stage_final_block(const Combo<T>& mk, const Extr
 #pragma unroll
             for (int c = 0; c < 3; ++c) f[k][c] = fs.f[k][ci.off + c * N + ci.cell];
         T m[3], fS[3];
-        stage_rhs<T>(mk, ex, ph, ci, N, m, fS);
+        stage_rhs<T, NG>(mk, ex, ph, ci, N, m, fS);
         double e2 = 0.0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -350,11 +389,10 @@ __device__ __forceinline__ void stage_final_block(const Combo<T>& mk, const Extr
 }
 
 // ---------------------------------------------------------------------------
-// Whole sub-steps for small meshes (stage_direct_ok): the stage input M_k of
-// Eq. (4) is formed at every stencil read and Eq. (6) at the stage's own time
-// from the stored fields, so a sub-step is one launch with no stage input and
-// no Eq. (6) field in memory.  The sums are those of combine_* and epoly_*,
-// term for term: the same bits.
+// ABM2's extrapolated evaluation in one launch: the predicted state, a
+// combination of at most two derivatives, is formed at every stencil read and
+// Eq. (6) from the stored fields, so neither is in memory.  The sums are those of
+// combine_* and epoly_*, term for term: the same bits.
 
 // M_k at flat index i of the sample's [3][N] block (NF terms)
 template <typename T, int NF>
@@ -369,11 +407,13 @@ struct ComboField {
     }
 };
 
-// F of the sub-step; NG: at most this many Eq. (6) nodes (loads past ex.n read
-// node 0 and are left out of the sum)
+// F at the predicted state; NG: at most this many Eq. (6) nodes (as stage_rhs)
 template <typename T, int NF, int NG>
-__device__ __forceinline__ void stage_direct_rhs(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
-                                                 const CellIdx& ci, long N, T m[3], T f[3]) {
+__device__ __forceinline__ void predicted_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
+                                                T* __restrict__ F, const CellBlk& k) {
+    const long N = (long)ph.nx * ph.ny * ph.nz;
+    const CellIdx ci = cell_index(ph, k);
+    if (!ci.ok) return;
     const long i0 = ci.off + ci.cell;
     T gk[NG][3];
 #pragma unroll
@@ -383,7 +423,7 @@ __device__ __forceinline__ void stage_direct_rhs(const Combo<T>& mk, const Extra
         for (int c = 0; c < 3; ++c) gk[i][c] = p[i0 + c * N];
     }
     const ComboField<T, NF> M{mk, ci.off};
-    T hd[3], H[3];
+    T hd[3], H[3], m[3], f[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         T g = NG == 1 ? gk[0][c] : T(0);
@@ -398,68 +438,8 @@ __device__ __forceinline__ void stage_direct_rhs(const Combo<T>& mk, const Extra
     }
     heff_at(M, N, ci.cell, ci.x, ci.y, ci.z, ci.b, ph, hd, m, H);
     llg_at(m, H, ph, f);
-}
-
-template <typename T, int NF, int NG>
-__device__ __forceinline__ void stage_direct_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
-                                                   T* __restrict__ F, const CellBlk& k) {
-    const long N = (long)ph.nx * ph.ny * ph.nz;
-    const CellIdx ci = cell_index(ph, k);
-    if (!ci.ok) return;
-    T m[3], f[3];
-    stage_direct_rhs<T, NF, NG>(mk, ex, ph, ci, N, m, f);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) F[ci.off + c * N + ci.cell] = f[c];
-}
-
-// the last sub-step with Eq. (3) and the estimate (stage_final_block).  mnew may
-// be M0, but not mk's base or one of its terms: neighbours still read those.
-template <typename T, int NF, int NG>
-__device__ __forceinline__ void stage_direct_final_block(const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
-                                                         const T* M0, const Final<T>& fs, double inv_ms,
-                                                         T* mnew, double* __restrict__ parts, const CellBlk& k) {
-    const long N = (long)ph.nx * ph.ny * ph.nz;
-    const CellIdx ci = cell_index(ph, k);
-    const int tid = k.iy * k.tx + k.ix;
-    double emax = 0.0;
-    if (ci.ok) {
-        const long i0 = ci.off + ci.cell;
-        constexpr int NS = MAX_F - 1;  // stored derivatives, the last entry is this stage's own
-        T m0[3], f[NS][3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) m0[c] = M0[i0 + c * N];
-#pragma unroll
-        for (int l = 0; l < NS; ++l) {
-            const T* p = l < fs.n - 1 ? fs.f[l] : M0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) f[l][c] = p[i0 + c * N];
-        }
-        T m[3], fS[3];
-        stage_direct_rhs<T, NF, NG>(mk, ex, ph, ci, N, m, fS);
-        double e2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            T v = m0[c];
-            double d = 0.0;
-#pragma unroll
-            for (int l = 0; l < NS; ++l) {
-                const T s = v + fs.cb[l] * f[l][c];
-                const double e = d + fs.ce[l] * (double)f[l][c];
-                v = l < fs.n - 1 ? s : v;
-                d = l < fs.n - 1 ? e : d;
-            }
-            v += fs.cb[fs.n - 1] * fS[c];
-            mnew[i0 + c * N] = v;
-            if (fs.err) {
-                d += fs.ce[fs.n - 1] * (double)fS[c];
-                e2 += d * d;
-            }
-        }
-        emax = sqrt(e2) * inv_ms;
-        if (e2 != e2) emax = e2;
-    }
-    const double bm = block_max(emax, tid);
-    if (tid == 0) parts[k.by * k.gx + k.bx] = bm;
+    for (int c = 0; c < 3; ++c) F[i0 + c * N] = f[c];
 }
 
 template <typename T, int NF>

@@ -194,14 +194,17 @@ constexpr int NVAR_XFWD = 3, NVAR_COL = 3, NVAR_ZMUL = 3, NVAR_XINV = 3;
 // Stage kernels (llg.hip).
 template <typename T>
 hipError_t launch_combine(hipStream_t s, long n, const Combo<T>& c, T* out);
-// Optional second output of a sub-step kernel: the next stage input
-// mnext = m0 + cnext F of Eq. (4) when that stage's row holds only the stage
-// just formed (as in RK4), so no combine pass is needed for it.
+// Optional second output of a sub-step kernel: the next stage input of Eq. (4),
+// mnext = m0 + sum_l coef[l] f[l] + cnext F (nf terms of earlier stages, then the
+// stage just formed), so no combination pass is needed for it.
 template <typename T>
 struct NextStage {
     const T* m0;
     T* mnext;
     T cnext;
+    int nf;
+    const T* f[MAX_F - 1];
+    T coef[MAX_F - 1];
 };
 
 // Sub-step F at the stage input mk.base (mk.nf must be 0: a stage input with
@@ -222,14 +225,12 @@ hipError_t launch_stage_ep(hipStream_t s, const Combo<T>& mk, const Extrap<T>& e
 template <typename T>
 hipError_t launch_stage_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, const T* M0,
                               const Final<T>& fs, double inv_ms, T* mnew, double* parts);
-// Sub-steps of small meshes, stage input and Eq. (6) field formed inside
-// (cells.hpp): mk with its terms, ex.n nodes of the stage's own time
-bool stage_direct_ok(long cells, size_t real_bytes, int terms);
+// Whether the sub-steps of a mesh form Eq. (6) themselves (ex.n stored fields)
+// instead of reading fields that launch_epoly or launch_stage_ep formed
+bool eq6_inside(long cells, size_t real_bytes);
+// ABM2's sub-step at the predicted state mk (1 or 2 terms), formed inside
 template <typename T>
-hipError_t launch_stage_direct(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F);
-template <typename T>
-hipError_t launch_stage_direct_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
-                                     const T* M0, const Final<T>& fs, double inv_ms, T* mnew, double* parts);
+hipError_t launch_predicted(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F);
 template <typename T>
 hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms, T* mnew,
                         double* parts, int nparts);

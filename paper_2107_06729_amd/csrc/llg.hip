@@ -49,31 +49,22 @@ __global__ __launch_bounds__(NTS) void k_epoly_scalar(long n, EPoly<T> ep) {
     epoly_scalar_blocks<T, NG>(n, ep, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int NF, int NG>
-__global__ __launch_bounds__(NTS) void k_stage_direct(Combo<T> mk, Extrap<T> ex, Phys<T> ph, T* __restrict__ F, int tx,
-                                                      int ry) {
-    stage_direct_block<T, NF, NG>(mk, ex, ph, F, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
-                                                         (int)threadIdx.x, (int)threadIdx.y});
-}
-
-template <typename T, int NF, int NG>
-__global__ __launch_bounds__(NTS) void k_stage_direct_final(Combo<T> mk, Extrap<T> ex, Phys<T> ph, const T* M0,
-                                                            Final<T> fs, double inv_ms, T* mnew,
-                                                            double* __restrict__ parts, int tx, int ry) {
-    stage_direct_final_block<T, NF, NG>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,
-                                        CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
-                                                (int)threadIdx.x, (int)threadIdx.y});
-}
-
 // 2-D grid of the stencil kernels: blockIdx.x over row groups, blockIdx.y
 // over x segments, blocks of tx x ry threads.  The block shape comes in as an
 // argument: reading blockDim costs a vector load from the dispatch packet
 // that every wave would wait for before its first stencil load.
-template <typename T>
+template <typename T, int NX, int NG>
 __global__ __launch_bounds__(NTS) void k_stage(Combo<T> mk, Extrap<T> ex, Phys<T> ph, T* __restrict__ F,
                                                NextStage<T> nx, int tx, int ry) {
-    stage_block<T>(mk, ex, ph, F, nx, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
+    stage_block<T, NX, NG>(mk, ex, ph, F, nx, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
                                              (int)threadIdx.x, (int)threadIdx.y});
+}
+
+template <typename T, int NF, int NG>
+__global__ __launch_bounds__(NTS) void k_predicted(Combo<T> mk, Extrap<T> ex, Phys<T> ph, T* __restrict__ F, int tx,
+                                                   int ry) {
+    predicted_block<T, NF, NG>(mk, ex, ph, F, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
+                                                      (int)threadIdx.x, (int)threadIdx.y});
 }
 
 template <typename T, int NG, int ND>
@@ -84,13 +75,13 @@ __global__ __launch_bounds__(NTS) void k_stage_ep(Combo<T> mk, Extrap<T> ex, EPo
                                       (int)threadIdx.y});
 }
 
-template <typename T, int NF>
+template <typename T, int NF, int NG>
 __global__ __launch_bounds__(NTS) void k_stage_final(Combo<T> mk, Extrap<T> ex, Phys<T> ph, const T* M0,
                                                      Final<T> fs, double inv_ms, T* mnew,
                                                      double* __restrict__ parts, int tx, int ry) {
-    stage_final_block<T, NF>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,
-                             CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)threadIdx.x,
-                                     (int)threadIdx.y});
+    stage_final_block<T, NF, NG>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,
+                                 CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)threadIdx.x,
+                                         (int)threadIdx.y});
 }
 
 template <typename T, int NF>
@@ -277,20 +268,45 @@ hipError_t launch_epoly(hipStream_t s, long n, const EPoly<T>& ep) {
     return hipGetLastError();
 }
 
+// NG = 1: one field; 6: Eq. (6) from ex.n stored ones
+static int node_bucket(int n) { return n == 1 ? 1 : n >= 2 && n <= MAX_HIST ? 6 : 0; }
+
 template <typename T>
 hipError_t launch_extrap_rhs(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F,
                              const NextStage<T>& nx) {
     const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
-    if (ex.n != 1 || mk.nf != 0) return hipErrorInvalidValue;
-    k_stage<T><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, nx, (int)cg.block.x, (int)cg.block.y);
-    return hipGetLastError();
+    const int ng = node_bucket(ex.n);
+    if (mk.nf != 0) return hipErrorInvalidValue;
+#define ST(X, G)                                                                                            \
+    if (nx.nf == X && ng == G) {                                                                            \
+        k_stage<T, X, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, nx, (int)cg.block.x, (int)cg.block.y); \
+        return hipGetLastError();                                                                           \
+    }
+    ST(0, 1) ST(1, 1) ST(2, 1) ST(3, 1) ST(4, 1) ST(5, 1) ST(6, 1)
+    ST(0, 6) ST(1, 6) ST(2, 6) ST(3, 6) ST(4, 6) ST(5, 6) ST(6, 6)
+#undef ST
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_predicted(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F) {
+    const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
+    const int tx = (int)cg.block.x, ry = (int)cg.block.y, ng = node_bucket(ex.n);
+#define PR(K, G)                                                                  \
+    if (mk.nf == K && ng == G) {                                                  \
+        k_predicted<T, K, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, tx, ry); \
+        return hipGetLastError();                                                 \
+    }
+    PR(1, 1) PR(2, 1) PR(1, 6) PR(2, 6)
+#undef PR
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t launch_stage_ep(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const EPoly<T>& ep, int jself,
                            const Phys<T>& ph, T* F, const NextStage<T>& nx) {
     const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
-    if (ex.n != 1 || mk.nf != 0 || jself >= ep.nd) return hipErrorInvalidValue;
+    if (ex.n != 1 || mk.nf != 0 || jself >= ep.nd || nx.nf != 0) return hipErrorInvalidValue;
     const int tx = (int)cg.block.x, ry = (int)cg.block.y;
 #define EPS(G, D)                                                                                          \
     if (ep.ng == G && ep.nd == D) {                                                                        \
@@ -307,12 +323,17 @@ template <typename T>
 hipError_t launch_stage_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, const T* M0,
                               const Final<T>& fs, double inv_ms, T* mnew, double* parts) {
     const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
-    if (ex.n != 1 || mk.nf != 0) return hipErrorInvalidValue;
+    const int ng = node_bucket(ex.n);
+    if (ng == 0 || mk.nf != 0) return hipErrorInvalidValue;
     switch (fs.n) {
-#define SF(K)                                                                                                   \
-    case K:                                                                                                    \
-        k_stage_final<T, K><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, M0, fs, inv_ms, mnew, parts, (int)cg.block.x, \
-                                                         (int)cg.block.y);                                       \
+#define SF(K)                                                                                                 \
+    case K:                                                                                                  \
+        if (ng == 1)                                                                                         \
+            k_stage_final<T, K, 1><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,     \
+                                                                (int)cg.block.x, (int)cg.block.y);           \
+        else                                                                                                 \
+            k_stage_final<T, K, 6><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, M0, fs, inv_ms, mnew, parts,     \
+                                                                (int)cg.block.x, (int)cg.block.y);           \
         break;
         SF(1) SF(2) SF(3) SF(4) SF(5) SF(6) SF(7) SF(8)
 #undef SF
@@ -321,55 +342,14 @@ hipError_t launch_stage_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>
     return hipGetLastError();
 }
 
-// Sub-steps with at most two terms are faster in one launch at every size (ABM2
-// p = 2, whole adaptive steps: 32x32x2 58.7 -> 30.1 us, 256x256x16 135.6 -> 126.8 FP32).
-// With more, each term is read again at the neighbours, which pays while the
-// fields stay near the CU and the launches saved (12 of 23 in a Dormand-Prince
-// step) count: up to 512 KiB a component.  RKDP54 p = 4, whole steps with and
-// without: 256x64x1 FP32 64 / 86 us, 256x256x2 79 / 97, 256x256x4 102 / 98,
-// 128x128x32 202 / 159; FP64 128x128x4 77 / 91, 256x256x2 113 / 102.
-bool stage_direct_ok(long cells, size_t real_bytes, int terms) {
-    return terms <= 2 || cells * (long)real_bytes <= (512L << 10);
-}
-
-#define DIRECT_CASES(M) \
-    M(0, 1) M(1, 1) M(2, 1) M(3, 1) M(4, 1) M(5, 1) M(6, 1) M(7, 1) M(0, 6) M(1, 6) M(2, 6) M(3, 6) M(4, 6) M(5, 6) \
-        M(6, 6) M(7, 6)
-
-template <typename T>
-hipError_t launch_stage_direct(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph, T* F) {
-    const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
-    const int tx = (int)cg.block.x, ry = (int)cg.block.y;
-    if (ex.n < 1 || ex.n > MAX_HIST) return hipErrorInvalidValue;
-    const int ng = ex.n == 1 ? 1 : 6;
-#define SD(K, G)                                                                             \
-    if (mk.nf == K && ng == G) {                                                             \
-        k_stage_direct<T, K, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, tx, ry);         \
-        return hipGetLastError();                                                            \
-    }
-    DIRECT_CASES(SD)
-#undef SD
-    return hipErrorInvalidValue;
-}
-
-template <typename T>
-hipError_t launch_stage_direct_final(hipStream_t s, const Combo<T>& mk, const Extrap<T>& ex, const Phys<T>& ph,
-                                     const T* M0, const Final<T>& fs, double inv_ms, T* mnew, double* parts) {
-    const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
-    const int tx = (int)cg.block.x, ry = (int)cg.block.y;
-    if (ex.n < 1 || ex.n > MAX_HIST || fs.n < 1 || fs.n > MAX_F || mnew == mk.base) return hipErrorInvalidValue;
-    const int ng = ex.n == 1 ? 1 : 6;
-#define SD(K, G)                                                                                            \
-    if (mk.nf == K && ng == G) {                                                                            \
-        k_stage_direct_final<T, K, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, M0, fs, inv_ms, mnew, parts, \
-                                                                   tx, ry);                                 \
-        return hipGetLastError();                                                                           \
-    }
-    DIRECT_CASES(SD)
-#undef SD
-    return hipErrorInvalidValue;
-}
-#undef DIRECT_CASES
+// Eq. (6) inside a sub-step saves the launch that forms its fields and the first
+// sub-step's writes of them, and costs p + 1 field reads in each sub-step instead
+// of one.  Inside against fields, one adaptive step (us):
+//   RKDP54 p = 4:  256x64x1 58 / 69   256x256x2 71 / 77   256x256x4 84 / 82
+//                  128x128x32 150 / 140   256x256x16 249 / 223 (FP64 497 / 439)
+//   RK23 p = 3:    32x32x2 36 / 63   256x256x2 47 / 65   256x256x16 155 / 156
+// The launch counts up to planes of 512 KiB a component; beyond, the reads do.
+bool eq6_inside(long cells, size_t real_bytes) { return cells * (long)real_bytes <= 512L << 10; }
 
 template <typename T>
 hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms, T* mnew,
@@ -431,10 +411,7 @@ hipError_t launch_cast(hipStream_t s, long n, const double* src, T* dst) {
 }
 
 #define INST(T)                                                                                                  \
-    template hipError_t launch_stage_direct<T>(hipStream_t, const Combo<T>&, const Extrap<T>&, const Phys<T>&, T*); \
-    template hipError_t launch_stage_direct_final<T>(hipStream_t, const Combo<T>&, const Extrap<T>&,             \
-                                                     const Phys<T>&, const T*, const Final<T>&, double, T*,      \
-                                                     double*);                                                   \
+    template hipError_t launch_predicted<T>(hipStream_t, const Combo<T>&, const Extrap<T>&, const Phys<T>&, T*);   \
     template hipError_t launch_combine<T>(hipStream_t, long, const Combo<T>&, T*);                               \
     template hipError_t launch_epoly<T>(hipStream_t, long, const EPoly<T>&);                                     \
     template hipError_t launch_extrap_rhs<T>(hipStream_t, const Combo<T>&, const Extrap<T>&, const Phys<T>&, T*,   \

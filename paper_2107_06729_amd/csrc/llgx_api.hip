@@ -640,9 +640,11 @@ template <typename T>
 static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     const Tableau* tab = pl.tab;
     const double h = pl.h;
-    // Stage j reads M_j = M0 + h sum_l a_jl F_l (Eq. 4).  When row j holds only
-    // a_j,j-1 (RK4), the kernel that forms F_{j-1} also writes M_j, into one of
-    // two buffers taken in turn (the stencil of stage j-1 still reads M_{j-1}).
+    // Stage j reads M_j = M0 + h sum_l a_jl F_l (Eq. 4).  With extrapolation the
+    // kernel that forms F_{j-1} also writes M_j, into one of two buffers taken in
+    // turn (the stencil of stage j-1 still reads M_{j-1}); stage 1's pass and
+    // job-table launches only where row j holds nothing but a_j,j-1 (`chained`).
+    // What is left (M_1 of a retry, job tables) takes a combination pass.
     auto chained = [&](int j) {
         if (!pl.extrap || j < 1 || j >= tab->S || tab->a[j][j - 1] == 0.0) return false;
         for (int l = 0; l + 1 < j; ++l)
@@ -668,16 +670,8 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     std::vector<int> field_of(tab->S, -1);
     bool fuse_ep = false;
     EPoly<T> ep_fused{};
-    // sub-steps in one launch each, unless the stage inputs are all chained and
-    // the first sub-step forms the Eq. (6) fields (RK4: as few launches already)
-    int terms = 0;  // most terms of a stage input that is not chained
-    for (int k = 1; k < tab->S; ++k) {
-        int nf = 0;
-        for (int l = 0; l < k; ++l) nf += tab->a[k][l] != 0.0;
-        if (!chained(k)) terms = std::max(terms, nf);
-    }
-    const bool direct = pl.extrap && !c->rec && (terms > 0 || tab->S < 3) &&
-                        stage_direct_ok(c->ncell * c->nb, sizeof(T), terms);
+    // Eq. (6) inside every sub-step instead of in fields of its own
+    const bool inside = pl.extrap && !c->rec && (tab->S == 2 || eq6_inside(c->ncell * c->nb, sizeof(T)));
     if (pl.extrap) {
         for (auto& hh : c->hist) {
             nodes.push_back(hh.t - c->t);
@@ -696,7 +690,7 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             }
             field_of[k] = j;
         }
-        if (!times.empty() && !direct) {
+        if (!times.empty() && (!inside || (times.size() <= 2 && tab->S >= 3))) {
             EPoly<T> ep{};
             ep.ng = (int)nodes.size();
             ep.nd = (int)times.size();
@@ -748,38 +742,7 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             cb.coef[cb.nf] = (T)(h * tab->a[k][l]);
             cb.nf++;
         }
-        if (direct) {
-            Extrap<T> ex{};
-            ex.n = 1;
-            ex.w[0] = T(1);
-            ex.g[0] = (const T*)c->G[pl.slot0];
-            if (field_of[k] >= 0) {
-                ex.n = (int)nodes.size();
-                const std::vector<double> w = lagrange(nodes, tab->c[k] * h);
-                for (int i = 0; i < ex.n; ++i) {
-                    ex.g[i] = (const T*)c->G[slots[i]];
-                    ex.w[i] = (T)w[i];
-                }
-            }
-            const bool last = k == tab->S - 1;
-            if (formed[k]) {
-                cb = plain<T>(mkbuf(k));
-            } else if (last && pl.in_place) {
-                // Eq. (3) overwrites M0, which the stage input's neighbours would read
-                PROF(LLGX_K_COMBINE);
-                HIPCHK(c, launch_combine<T>(c->stream, 3 * c->ncell * c->nb, cb, (T*)mkbuf(k)));
-                cb = plain<T>(mkbuf(k));
-            }
-            ProfScope ps(c, last ? LLGX_K_FINAL : LLGX_K_EXTRAP);
-            if (last) {
-                add_final(k);  // own derivative, last entry
-                HIPCHK(c, launch_stage_direct_final<T>(c->stream, cb, ex, phys<T>(c), (const T*)c->M, fs, 1.0 / c->p.Ms,
-                                                       (T*)(pl.in_place ? c->M : c->Mnew), c->parts));
-                fused_final = true;
-            } else {
-                HIPCHK(c, launch_stage_direct<T>(c->stream, cb, ex, phys<T>(c), (T*)c->F[k]));
-            }
-        } else if (pl.extrap) {
+        if (pl.extrap) {
             if (formed[k]) {
                 cb = plain<T>(mkbuf(k));
             } else if (cb.nf > 0) {
@@ -795,6 +758,14 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             ex.n = 1;
             ex.w[0] = T(1);
             ex.g[0] = field_of[k] < 0 ? (const T*)c->G[pl.slot0] : (const T*)c->E[field_of[k]];
+            if (inside && !fuse_ep && field_of[k] >= 0) {
+                ex.n = (int)nodes.size();
+                const std::vector<double> w = lagrange(nodes, tab->c[k] * h);
+                for (int i = 0; i < ex.n; ++i) {
+                    ex.g[i] = (const T*)c->G[slots[i]];
+                    ex.w[i] = (T)w[i];
+                }
+            }
             const bool with_ep = fuse_ep && k == 1;
             ProfScope ps(c, k == tab->S - 1 ? LLGX_K_FINAL : with_ep ? LLGX_K_EPOLY : LLGX_K_EXTRAP);
             if (k == tab->S - 1) {
@@ -808,9 +779,17 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
                                                     1.0 / c->p.Ms, mnew, c->parts));
                 fused_final = true;
             } else {
-                NextStage<T> nx{nullptr, nullptr, T(0)};
-                if (chained(k + 1)) {
-                    nx = NextStage<T>{(const T*)c->M, (T*)mkbuf(k + 1), (T)(h * tab->a[k + 1][k])};
+                NextStage<T> nx{};
+                if (chained(k + 1) || !(c->rec || with_ep)) {
+                    nx.m0 = (const T*)c->M;
+                    nx.mnext = (T*)mkbuf(k + 1);
+                    nx.cnext = (T)(h * tab->a[k + 1][k]);
+                    for (int l = 0; l < k; ++l) {
+                        if (tab->a[k + 1][l] == 0.0) continue;
+                        nx.f[nx.nf] = (const T*)c->F[l];
+                        nx.coef[nx.nf] = (T)(h * tab->a[k + 1][l]);
+                        nx.nf++;
+                    }
                     formed[k + 1] = true;
                 }
                 if (c->rec)
@@ -985,8 +964,7 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             pr.coef[1] = (T)(-0.5 * h * r);
             pr.nf = 2;
         }
-        const bool direct = extrap && stage_direct_ok(c->ncell * c->nb, sizeof(T), pr.nf);
-        if (!direct) {
+        if (!extrap) {
             PROF(LLGX_K_COMBINE);
             HIPCHK(c, launch_combine<T>(c->stream, 3 * c->ncell * c->nb, pr, (T*)c->Mk));
         }
@@ -996,7 +974,7 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
             ex.w[0] = T(1);
             if (p == 0) {
                 ex.g[0] = (const T*)c->G[c->abm_slot];
-            } else if (direct) {
+            } else {
                 std::vector<double> nodes;
                 for (int i = 0; i < p; ++i) {
                     nodes.push_back(c->hist[i].t - c->t);
@@ -1007,32 +985,9 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
                 const std::vector<double> w = lagrange(nodes, h);
                 for (int i = 0; i <= p; ++i) ex.w[i] = (T)w[i];
                 ex.n = p + 1;
-            } else {
-                std::vector<double> nodes;
-                EPoly<T> ep{};
-                ep.ng = p + 1;
-                ep.nd = 1;
-                for (int i = 0; i < p; ++i) {
-                    nodes.push_back(c->hist[i].t - c->t);
-                    ep.g[i] = (const T*)c->G[c->hist[i].slot];
-                }
-                nodes.push_back(0.0);
-                ep.g[p] = (const T*)c->G[c->abm_slot];
-                const std::vector<double> w = lagrange(nodes, h);
-                for (int i = 0; i <= p; ++i) ep.w[0][i] = (T)w[i];
-                ep.out[0] = (T*)c->E[0];
-                {
-                    PROF(LLGX_K_EPOLY);
-                    HIPCHK(c, launch_epoly<T>(c->stream, 3 * c->ncell * c->nb, ep));
-                }
-                ex.g[0] = (const T*)c->E[0];
             }
             PROF(LLGX_K_EXTRAP);
-            if (direct)
-                HIPCHK(c, launch_stage_direct<T>(c->stream, pr, ex, phys<T>(c), (T*)c->F[1]));
-            else
-                HIPCHK(c, launch_extrap_rhs<T>(c->stream, plain<T>(c->Mk), ex, phys<T>(c), (T*)c->F[1],
-                                               NextStage<T>{nullptr, nullptr, T(0)}));
+            HIPCHK(c, launch_predicted<T>(c->stream, pr, ex, phys<T>(c), (T*)c->F[1]));
             c->n_extrap++;
         } else {
             XinvOut out{nullptr, c->F[1], nullptr, nullptr, 0.0};

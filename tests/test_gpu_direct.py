@@ -1,8 +1,9 @@
-"""Sub-steps in one launch (stage input and Eq. (6) field formed inside) against
-the separate combination, Eq. (6) and stage launches: job-table steps of a batch
-keep the separate ones, forked-stream steps take the single launch on these
-meshes, and the two must agree bit for bit for every tableau, order and number of
-terms, with empty cells and with rows that end inside a block."""
+"""Sub-steps that write the next stage input themselves, and form Eq. (6) inside
+on small meshes, against the separate combination, Eq. (6) and stage launches:
+job-table steps of a batch keep the separate ones, forked-stream steps take the
+fused ones, and the two must agree bit for bit for every tableau, order and number
+of terms, with empty cells, with rows that end inside a block and on both sides of
+the mesh size up to which Eq. (6) is formed inside."""
 
 import numpy as np
 import pytest
@@ -15,15 +16,17 @@ pytestmark = pytest.mark.gpu
 CELL = (4e-9, 4e-9, 3e-9)
 
 
-@pytest.mark.parametrize("prec", ["f32", "f64"])
+SMALL, LARGE = [(21, 13, 3), (70, 9, 1)], [(70, 64, 32), (21, 13, 3)]
+
+
+@pytest.mark.parametrize("meshes,prec", [(SMALL, "f32"), (SMALL, "f64"), (LARGE, "f32")])
 @pytest.mark.parametrize("method,p", [("RK23", 0), ("RK23", 3), ("RKF45", 1), ("RKCK45", 4), ("RKDP54", 5),
                                       ("RKF56", 2), ("HEUN", 2)])
-def test_direct_equals_separate(method, p, prec):
+def test_direct_equals_separate(method, p, meshes, prec):
     import torch
 
     import paper_2107_06729_amd as llgx
     log(f"direct {method} {p} {prec}")
-    meshes = [(21, 13, 3), (70, 9, 1)]
     stream = torch.cuda.Stream()
     got = []
     for launch in ("jobs", "streams"):
