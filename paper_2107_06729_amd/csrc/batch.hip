@@ -157,6 +157,7 @@ __device__ __forceinline__ NextStage<T> ld(const NextStage<T>* p) {
     n.mnext = gload(&p->mnext);
     n.cnext = sload(&p->cnext);
     n.nf = 0;  // job-table stages form chained inputs only
+    n.na = 0;
     return n;
 }
 

@@ -205,6 +205,11 @@ struct NextStage {
     int nf;
     const T* f[MAX_F - 1];
     T coef[MAX_F - 1];
+    // na > 0 (at most 2): in place of F the kernel writes Eq. (3) up to this
+    // stage, m0 + sum_l ca[l] fa[l] + cown F
+    int na;
+    const T* fa[2];
+    T ca[2], cown;
 };
 
 // Sub-step F at the stage input mk.base (mk.nf must be 0: a stage input with

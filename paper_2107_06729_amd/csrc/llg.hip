@@ -53,11 +53,11 @@ __global__ __launch_bounds__(NTS) void k_epoly_scalar(long n, EPoly<T> ep) {
 // over x segments, blocks of tx x ry threads.  The block shape comes in as an
 // argument: reading blockDim costs a vector load from the dispatch packet
 // that every wave would wait for before its first stencil load.
-template <typename T, int NX, int NG>
+template <typename T, int NX, int NG, int NA>
 __global__ __launch_bounds__(NTS) void k_stage(Combo<T> mk, Extrap<T> ex, Phys<T> ph, T* __restrict__ F,
                                                NextStage<T> nx, int tx, int ry) {
-    stage_block<T, NX, NG>(mk, ex, ph, F, nx, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
-                                             (int)threadIdx.x, (int)threadIdx.y});
+    stage_block<T, NX, NG, NA>(mk, ex, ph, F, nx, CellBlk{tx, ry, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y,
+                                                          (int)threadIdx.x, (int)threadIdx.y});
 }
 
 template <typename T, int NF, int NG>
@@ -276,14 +276,15 @@ hipError_t launch_extrap_rhs(hipStream_t s, const Combo<T>& mk, const Extrap<T>&
                              const NextStage<T>& nx) {
     const CellGrid cg = cell_grid(ph.nx, ph.ny, ph.nz, ph.nb);
     const int ng = node_bucket(ex.n);
-    if (mk.nf != 0) return hipErrorInvalidValue;
-#define ST(X, G)                                                                                            \
-    if (nx.nf == X && ng == G) {                                                                            \
-        k_stage<T, X, G><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, nx, (int)cg.block.x, (int)cg.block.y); \
-        return hipGetLastError();                                                                           \
+    if (mk.nf != 0 || (nx.na != 0 && !nx.mnext)) return hipErrorInvalidValue;
+#define ST(X, G, A)                                                                                            \
+    if (nx.nf == X && ng == G && nx.na == A) {                                                                 \
+        k_stage<T, X, G, A><<<cg.grid, cg.block, 0, s>>>(mk, ex, ph, F, nx, (int)cg.block.x, (int)cg.block.y); \
+        return hipGetLastError();                                                                              \
     }
-    ST(0, 1) ST(1, 1) ST(2, 1) ST(3, 1) ST(4, 1) ST(5, 1) ST(6, 1)
-    ST(0, 6) ST(1, 6) ST(2, 6) ST(3, 6) ST(4, 6) ST(5, 6) ST(6, 6)
+    ST(0, 1, 0) ST(1, 1, 0) ST(2, 1, 0) ST(3, 1, 0) ST(4, 1, 0) ST(5, 1, 0) ST(6, 1, 0)
+    ST(0, 6, 0) ST(1, 6, 0) ST(2, 6, 0) ST(3, 6, 0) ST(4, 6, 0) ST(5, 6, 0) ST(6, 6, 0)
+    ST(0, 1, 2) ST(0, 6, 2)
 #undef ST
     return hipErrorInvalidValue;
 }

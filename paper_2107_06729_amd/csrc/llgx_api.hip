@@ -731,6 +731,13 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
         const bool use_e = fs.err && tab->b[k] != tab->bh[k];
         if (use_b || use_e) add_final(k);
     }
+    // Fixed steps whose last input is chained and whose update takes two stages
+    // before the second last one (RK4): that one writes the sum of Eq. (3) so far
+    // in place of its derivative: it reads two fields more for it, the last one reads
+    // one instead of four (256x256x16 FP32, both: 25.8 us separate, 23.9 so).
+    const bool partial = pl.extrap && !c->rec && !fs.err && tab->S >= 4 && chained(tab->S - 1) && fs.n == 3 &&
+                         tab->b[tab->S - 2] != 0.0;
+    const T* base = (const T*)c->M;  // what the last sub-step adds fs to
     bool fused_final = false;
     for (int k = 1; k < tab->S; ++k) {
         Combo<T> cb{};
@@ -773,10 +780,10 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
                 T* mnew = (T*)(pl.in_place ? c->M : c->Mnew);
                 if (c->rec)
                     record(c, BK_STAGE_FINAL, fs.n,
-                           BStageFinal<T>{cb, ex, phys<T>(c), (const T*)c->M, fs, 1.0 / c->p.Ms, mnew, c->parts});
+                           BStageFinal<T>{cb, ex, phys<T>(c), base, fs, 1.0 / c->p.Ms, mnew, c->parts});
                 else
-                    HIPCHK(c, launch_stage_final<T>(c->stream, cb, ex, phys<T>(c), (const T*)c->M, fs,
-                                                    1.0 / c->p.Ms, mnew, c->parts));
+                    HIPCHK(c, launch_stage_final<T>(c->stream, cb, ex, phys<T>(c), base, fs, 1.0 / c->p.Ms, mnew,
+                                                    c->parts));
                 fused_final = true;
             } else {
                 NextStage<T> nx{};
@@ -791,6 +798,15 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
                         nx.nf++;
                     }
                     formed[k + 1] = true;
+                }
+                if (partial && k == tab->S - 2) {
+                    for (nx.na = 0; nx.na < 2; ++nx.na) {
+                        nx.fa[nx.na] = fs.f[nx.na];
+                        nx.ca[nx.na] = fs.cb[nx.na];
+                    }
+                    nx.cown = fs.cb[2];
+                    fs.n = 0;
+                    base = (const T*)c->F[k];
                 }
                 if (c->rec)
                     record(c, BK_STAGE, 0, BStage<T>{cb, ex, phys<T>(c), (T*)c->F[k], nx});

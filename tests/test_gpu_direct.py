@@ -21,7 +21,7 @@ SMALL, LARGE = [(21, 13, 3), (70, 9, 1)], [(70, 64, 32), (21, 13, 3)]
 
 @pytest.mark.parametrize("meshes,prec", [(SMALL, "f32"), (SMALL, "f64"), (LARGE, "f32")])
 @pytest.mark.parametrize("method,p", [("RK23", 0), ("RK23", 3), ("RKF45", 1), ("RKCK45", 4), ("RKDP54", 5),
-                                      ("RKF56", 2), ("HEUN", 2)])
+                                      ("RKF56", 2), ("HEUN", 2), ("RK4", 0), ("RK4", 4)])
 def test_direct_equals_separate(method, p, meshes, prec):
     import torch
 
