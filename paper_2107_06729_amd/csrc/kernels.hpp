@@ -239,7 +239,8 @@ hipError_t launch_predicted(hipStream_t s, const Combo<T>& mk, const Extrap<T>& 
 template <typename T>
 hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const Final<T>& fs, double inv_ms, T* mnew,
                         double* parts, int nparts);
-hipError_t launch_reduce_max(hipStream_t s, const double* parts, int nparts, double* out);
+// nout partials of the maximum of nparts values (NaN propagates)
+hipError_t launch_reduce_max(hipStream_t s, const double* parts, int nparts, double* out, int nout);
 // per-block partials (nparts blocks) of max over cells |v| / Ms, for launch_reduce_max
 template <typename T>
 hipError_t launch_max_norm(hipStream_t s, long ncell, int nb, const T* v, double inv_ms, double* parts, int nparts);

@@ -92,9 +92,9 @@ __global__ __launch_bounds__(NTS) void k_final(long ncell, int nb, const T* base
 
 __global__ __launch_bounds__(NTS) void k_reduce_max(const double* __restrict__ parts, int n, double* __restrict__ out) {
     double m = 0.0;
-    for (int i = threadIdx.x; i < n; i += NTS) m = nan_max(m, parts[i]);
+    for (int i = (int)(blockIdx.x * NTS + threadIdx.x); i < n; i += (int)gridDim.x * NTS) m = nan_max(m, parts[i]);
     const double bm = block_max(m, threadIdx.x);
-    if (threadIdx.x == 0) out[0] = bm;
+    if (threadIdx.x == 0) out[blockIdx.x] = bm;
 }
 
 // Per-block partials of max over cells of |v| / Ms for a vector field v
@@ -365,8 +365,8 @@ hipError_t launch_final(hipStream_t s, long ncell, int nb, const T* base, const 
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_max(hipStream_t s, const double* parts, int nparts, double* out) {
-    k_reduce_max<<<1, NTS, 0, s>>>(parts, nparts, out);
+hipError_t launch_reduce_max(hipStream_t s, const double* parts, int nparts, double* out, int nout) {
+    k_reduce_max<<<(unsigned)nout, NTS, 0, s>>>(parts, nparts, out);
     return hipGetLastError();
 }
 

@@ -126,8 +126,9 @@ struct Ctx {
     int nparts = 1;             // blocks of the 1-D reduction kernels
     long nparts_alloc = 1;      // capacity of parts (also covers the 2-D cell grid)
     double* scal = nullptr;     // [0] error norm, [1..3] sums for <M>
-    double* err_host = nullptr; // the error norm in pinned host memory (adaptive steps), written by
-    double* err_dev = nullptr;  // the reduction through its device address
+    double* err_host = nullptr; // partial maxima of the error estimate in pinned host memory (adaptive
+    double* err_dev = nullptr;  // steps, ERR_SLOTS), their device address, and how many of them the
+    int err_n = 0;              // latest attempt writes
     int* empty_flag = nullptr;  // device: [0] some cell of M has M = 0; [1] always 1
     bool empty_stale = false;   // M changed since the flag was set (batches: see check_stepper)
     // during a field call: flag [1], so every neighbour is tested (the same result;
@@ -636,6 +637,49 @@ struct Plan {
     bool in_place;    // Eq. (3) update written over M0 (fixed steps: no retry needs M0)
 };
 
+// The error norm of adaptive attempts ends in pinned host memory, so an attempt
+// ends with one wait and the host takes the last maximum.  Up to ERR_SLOTS blocks
+// of the update write their maxima there themselves; a larger grid's are reduced to
+// one value per REDUCE of them first: one block alone took 4.0 us for the 8192
+// maxima of 128x128x32 cells, and 2.4 us as a launch of its own for 256
+// (an RK23 step at 32x32x2 36.3 us with it, 33.7 without)
+constexpr int ERR_SLOTS = 512, REDUCE = 1024;
+
+static llgx_status host_slots(Ctx* c) {
+    if (c->err_host) return LLGX_OK;
+    void* host = nullptr;
+    HIPCHK(c, hipHostMalloc(&host, ERR_SLOTS * sizeof(double), hipHostMallocMapped));
+    const hipError_t e = hipHostGetDevicePointer((void**)&c->err_dev, host, 0);
+    if (e != hipSuccess) {
+        (void)hipHostFree(host);
+        return c->fail(LLGX_E_HIP, "no device address of pinned memory: %s", hipGetErrorString(e));
+    }
+    c->err_host = (double*)host;
+    return LLGX_OK;
+}
+
+// where nred blocks of an update write their maxima
+static double* err_parts(Ctx* c, int nred) { return nred <= ERR_SLOTS ? c->err_dev : c->parts; }
+
+static llgx_status finish_err(Ctx* c, int nred) {
+    c->err_n = nred;
+    if (nred <= ERR_SLOTS) return LLGX_OK;
+    PROF(LLGX_K_OTHER);
+    c->err_n = std::min(ERR_SLOTS, (nred + REDUCE - 1) / REDUCE);
+    HIPCHK(c, launch_reduce_max(c->stream, c->parts, nred, c->err_dev, c->err_n));
+    return LLGX_OK;
+}
+
+// the error norm, after the stream was waited for; NaN propagates
+static double read_err(const Ctx* c) {
+    double m = 0.0;
+    for (int i = 0; i < c->err_n; ++i) {
+        const double v = ((volatile double*)c->err_host)[i];
+        m = std::isnan(v) || std::isnan(m) ? NAN : std::max(m, v);
+    }
+    return m;
+}
+
 template <typename T>
 static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     const Tableau* tab = pl.tab;
@@ -738,6 +782,8 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     const bool partial = pl.extrap && !c->rec && !fs.err && tab->S >= 4 && chained(tab->S - 1) && fs.n == 3 &&
                          tab->b[tab->S - 2] != 0.0;
     const T* base = (const T*)c->M;  // what the last sub-step adds fs to
+    const int nred = pl.extrap && tab->S > 1 ? (int)cell_grid(c->nx, c->ny, c->nz, c->nb).nblocks : c->nparts;
+    double* parts = pl.want_err && !c->rec ? err_parts(c, nred) : c->parts;
     bool fused_final = false;
     for (int k = 1; k < tab->S; ++k) {
         Combo<T> cb{};
@@ -780,10 +826,10 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
                 T* mnew = (T*)(pl.in_place ? c->M : c->Mnew);
                 if (c->rec)
                     record(c, BK_STAGE_FINAL, fs.n,
-                           BStageFinal<T>{cb, ex, phys<T>(c), base, fs, 1.0 / c->p.Ms, mnew, c->parts});
+                           BStageFinal<T>{cb, ex, phys<T>(c), base, fs, 1.0 / c->p.Ms, mnew, parts});
                 else
                     HIPCHK(c, launch_stage_final<T>(c->stream, cb, ex, phys<T>(c), base, fs, 1.0 / c->p.Ms, mnew,
-                                                    c->parts));
+                                                    parts));
                 fused_final = true;
             } else {
                 NextStage<T> nx{};
@@ -822,42 +868,22 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
             if (st) return st;
         }
     }
-    int nred = c->nparts;
-    if (fused_final) {
-        nred = (int)cell_grid(c->nx, c->ny, c->nz, c->nb).nblocks;
-    } else {
+    if (!fused_final) {
         PROF(LLGX_K_FINAL);
         T* mnew = (T*)(pl.in_place ? c->M : c->Mnew);
         if (c->rec)
             record(c, BK_FINAL, fs.n,
-                   BFinal<T>{c->ncell, c->nb, (const T*)c->M, fs, 1.0 / c->p.Ms, mnew, c->parts, c->nparts});
+                   BFinal<T>{c->ncell, c->nb, (const T*)c->M, fs, 1.0 / c->p.Ms, mnew, parts, c->nparts});
         else
-            HIPCHK(c, launch_final<T>(c->stream, c->ncell, c->nb, (const T*)c->M, fs, 1.0 / c->p.Ms, mnew, c->parts,
+            HIPCHK(c, launch_final<T>(c->stream, c->ncell, c->nb, (const T*)c->M, fs, 1.0 / c->p.Ms, mnew, parts,
                                       c->nparts));
     }
     if (pl.want_err) {
-        PROF(LLGX_K_OTHER);
         if (c->rec)
             c->rec_unsupported = true;
         else
-            HIPCHK(c, launch_reduce_max(c->stream, c->parts, nred, c->err_dev));
+            return finish_err(c, nred);
     }
-    return LLGX_OK;
-}
-
-// The slot the error norm of adaptive attempts is written to: pinned host
-// memory, so an attempt ends with the reduction and one wait (a copy of the
-// value to pageable memory cost a launch and a staging pass more)
-static llgx_status host_slot(Ctx* c) {
-    if (c->err_host) return LLGX_OK;
-    void* host = nullptr;
-    HIPCHK(c, hipHostMalloc(&host, sizeof(double), hipHostMallocMapped));
-    const hipError_t e = hipHostGetDevicePointer((void**)&c->err_dev, host, 0);
-    if (e != hipSuccess) {
-        (void)hipHostFree(host);
-        return c->fail(LLGX_E_HIP, "no device address of pinned memory: %s", hipGetErrorString(e));
-    }
-    c->err_host = (double*)host;
     return LLGX_OK;
 }
 
@@ -904,7 +930,7 @@ static llgx_status check_stepper(Ctx* c, const llgx_stepper* s, const Tableau** 
         if (st) return st;
     }
     if (s->adaptive) {
-        llgx_status st = host_slot(c);
+        llgx_status st = host_slots(c);
         if (st) return st;
     }
     if (s->method != c->cur_method || *p != c->cur_p) {
@@ -930,7 +956,7 @@ static llgx_status read_max_dmdt(Ctx* c, double* out) {
     }
     {
         PROF(LLGX_K_OTHER);
-        HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->scal + 4));
+        HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->scal + 4, 1));
     }
     HIPCHK(c, hipMemcpyAsync(out, c->scal + 4, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1031,15 +1057,15 @@ static llgx_status do_step_abm(Ctx* c, const llgx_stepper* s, int p, llgx_step_i
         {
             PROF(LLGX_K_FINAL);
             HIPCHK(c, launch_final<T>(c->stream, c->ncell, c->nb, (const T*)c->M, fs, 1.0 / c->p.Ms, (T*)c->Mnew,
-                                      c->parts, c->nparts));
+                                      s->adaptive ? err_parts(c, c->nparts) : c->parts, c->nparts));
         }
         if (!s->adaptive) break;
         {
-            PROF(LLGX_K_OTHER);
-            HIPCHK(c, launch_reduce_max(c->stream, c->parts, c->nparts, c->err_dev));
+            llgx_status st = finish_err(c, c->nparts);
+            if (st) return st;
         }
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        err = *(volatile double*)c->err_host;
+        err = read_err(c);
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
             err <= 0.0 ? s->c_max : std::min(std::max(std::pow(0.8 * s->e_max / err, 1.0 / 3.0), s->c_min), s->c_max);
@@ -1134,7 +1160,7 @@ static llgx_status do_step(Ctx* c, const llgx_stepper* s, llgx_step_info* info) 
             c->n_exact += later;
         if (!s->adaptive) break;
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        err = *(volatile double*)c->err_host;
+        err = read_err(c);
         if (!std::isfinite(err)) return c->fail(LLGX_E_NONFINITE, "non-finite error estimate at t=%g", c->t);
         const double cf =
             err <= 0.0 ? s->c_max
@@ -1969,7 +1995,7 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
             bt->err = "synchronisation failed";
             return LLGX_E_HIP;
         }
-        for (size_t g = 0; g < ng; ++g) errs[g] = *(volatile double*)bt->groups[g]->err_host;
+        for (size_t g = 0; g < ng; ++g) errs[g] = read_err(bt->groups[g]);
         err = 0.0;
         for (double e : errs) err = std::isfinite(e) && std::isfinite(err) ? std::max(err, e) : NAN;
         if (!std::isfinite(err)) {

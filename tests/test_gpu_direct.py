@@ -61,3 +61,29 @@ def test_field_call_finds_empty_cells_itself(op):
     s.set_m(to_dev(workloads.masked(M, workloads.checkerboard_mask(n, 4)), "f64"))
     # the state's flag does not reach a field call
     assert np.array_equal(to_host(getattr(s, op)(to_dev(M, "f64"))), full)
+
+
+# blocks of the update: 2 | 512 (all write their maximum to the host) | 520 and 2080
+# (reduced to 1 and 3 values first)
+@pytest.mark.parametrize("extrap", [None, 0])
+@pytest.mark.parametrize("n", [(33, 5, 1), (256, 256, 2), (256, 520, 1), (256, 520, 4)])
+def test_error_norm_of_a_heun_step(n, extrap):
+    """HEUN's estimate is (h/2)(F_1 - F_0) = M_new - M_0 - h F_0, so the reported
+    norm follows from public results.  Each term is rounded at 2^-53 Ms or less:
+    the difference of two M and the product leave below 2^-51 of Ms."""
+    import torch
+
+    import paper_2107_06729_amd as llgx
+    from tests.gpu_util import sim
+    s = sim(film(n, CELL), "f64", stream=torch.cuda.Stream())
+    M0 = workloads.random_m(n, 8e5, 96)
+    s.set_m(to_dev(M0, "f64"))
+    F0 = to_host(s.rhs(to_dev(M0, "f64")))
+    h = 1e-14
+    st = llgx.make_stepper("HEUN", extrap=extrap, h=h, adaptive=True, h_max=h, e_max=10.0)
+    info = s.step(st)
+    e = to_host(s.get_m()) - M0 - h * F0
+    want = float(np.sqrt((e * e).sum(axis=0)).max()) / 8e5
+    log(f"heun {n} {extrap}: {info['err']:.6e} want {want:.6e}")
+    assert want > 1e-6 and info["h_used"] == h
+    assert abs(info["err"] - want) < 2.0 ** -51 * 4
