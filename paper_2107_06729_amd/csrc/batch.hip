@@ -142,7 +142,7 @@ __device__ __forceinline__ Phys<T> ld(const Phys<T>* p) {
     return h;
 }
 __device__ __forceinline__ XinvOut ld(const XinvOut* p) {
-    XinvOut o;
+    XinvOut o{};
     o.h = gload(&p->h);
     o.f = gload(&p->f);
     o.g = gload(&p->g);

@@ -371,11 +371,37 @@ __device__ __forceinline__ void xinv_tile(const typename Spec<T, S>::elem* __res
         } else {
             const int y = tiled ? y0 + r : (int)g % ph.ny, z = tiled ? plane : (int)g / ph.ny;
             T m[3], H[3];
+            // Eq. (3) operands, loaded with the stencil (terms past nl read m0 and are
+            // left out)
+            T v[3], fl[3][3];
+            if constexpr (MODE == XINV_UPDATE) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) v[c] = ((const T*)out.m0)[vo + c * N + cell];
+#pragma unroll
+                for (int l = 0; l < 3; ++l) {
+                    const T* p = (const T*)(l < out.nl ? out.fl[l] : out.m0) + vo;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) fl[l][c] = p[c * N + cell];
+                }
+            }
             heff_at(PtrField<T>{M}, N, cell, x, y, z, b, ph, hd, m, H);
             if constexpr (MODE == XINV_HEFF) {
                 T* Ho = (T*)out.h + vo;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) Ho[c * N + cell] = H[c];
+            } else if constexpr (MODE == XINV_UPDATE) {
+                T F[3];
+                llg_at(m, H, ph, F);
+                T* Mn = (T*)out.mnew + vo;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+#pragma unroll
+                    for (int l = 0; l < 3; ++l) {
+                        const T s = v[c] + (T)out.cb[l] * fl[l][c];
+                        v[c] = l < out.nl ? s : v[c];
+                    }
+                    Mn[c * N + cell] = v[c] + (T)out.cb[out.nl] * F[c];
+                }
             } else {
                 T F[3];
                 llg_at(m, H, ph, F);

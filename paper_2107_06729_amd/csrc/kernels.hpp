@@ -105,7 +105,7 @@ struct Phys {
 };
 
 // Output selection of the inverse x pass.
-enum XinvMode { XINV_DEMAG = 0, XINV_HEFF = 1, XINV_RHS = 2 };
+enum XinvMode { XINV_DEMAG = 0, XINV_HEFF = 1, XINV_RHS = 2, XINV_UPDATE = 3 };
 
 struct XinvOut {
     void* h;       // demag field (XINV_DEMAG) or H_eff (XINV_HEFF), may be null in XINV_RHS
@@ -114,6 +114,13 @@ struct XinvOut {
     void* mnext;   // XINV_RHS, optional: next stage input M + cnext F (Eq. 4, a stage
                    // row whose only entry is the stage just formed)
     double cnext;
+    // XINV_UPDATE, the last stage of a step: Eq. (3), mnew = m0 + sum_l cb[l] fl[l]
+    // + cb[nl] F (nl <= 3 earlier stages), instead of f; mnew may be m0
+    const void* m0 = nullptr;
+    const void* fl[3] = {nullptr, nullptr, nullptr};
+    void* mnew = nullptr;
+    double cb[4] = {0.0, 0.0, 0.0, 0.0};
+    int nl = 0;
 };
 
 // Host-side launchers of the FFT passes (pass_x.hip, pass_col.hip, pass_z.hip)

@@ -784,6 +784,12 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
     const T* base = (const T*)c->M;  // what the last sub-step adds fs to
     const int nred = pl.extrap && tab->S > 1 ? (int)cell_grid(c->nx, c->ny, c->nz, c->nb).nblocks : c->nparts;
     double* parts = pl.want_err && !c->rec ? err_parts(c, nred) : c->parts;
+    // Steps with exact fields only and no estimate: the last stage's x pass writes
+    // Eq. (3) itself, unless its derivative is the next step's first.  One step (us),
+    // separate and so: HEUN FP32 32x32x2 22.9 / 21.3, 256x256x16 168 / 161; RK4 FP64
+    // 32x32x2 45.2 / 43.2, 256x256x16 633 / 619.
+    const bool update_inside = !pl.extrap && !c->rec && !pl.want_err && !tab->fsal && tab->S > 1 && fs.n >= 1 &&
+                               fs.n <= 4 && tab->b[tab->S - 1] != 0.0;
     bool fused_final = false;
     for (int k = 1; k < tab->S; ++k) {
         Combo<T> cb{};
@@ -863,12 +869,23 @@ static llgx_status enqueue_attempt(Ctx* c, const Plan& pl) {
                     HIPCHK(c, launch_extrap_rhs<T>(c->stream, cb, ex, phys<T>(c), (T*)c->F[k], nx));
             }
         } else {
-            XinvOut out{nullptr, c->F[k], nullptr};
-            llgx_status st = eval_exact<T>(c, cb, (T*)c->Mk, XINV_RHS, (const T*)c->Mk, out);
+            XinvOut out{nullptr, c->F[k], nullptr, nullptr, 0.0};
+            int mode = XINV_RHS;
+            if (update_inside && k == tab->S - 1) {
+                mode = XINV_UPDATE;
+                out.m0 = c->M;
+                out.mnew = pl.in_place ? c->M : c->Mnew;
+                for (int l = 0; l < fs.n; ++l) {
+                    out.cb[l] = fs.cb[l];
+                    if (l + 1 < fs.n) out.fl[l] = fs.f[l];
+                }
+                out.nl = fs.n - 1;
+            }
+            llgx_status st = eval_exact<T>(c, cb, (T*)c->Mk, mode, (const T*)c->Mk, out);
             if (st) return st;
         }
     }
-    if (!fused_final) {
+    if (!fused_final && !update_inside) {
         PROF(LLGX_K_FINAL);
         T* mnew = (T*)(pl.in_place ? c->M : c->Mnew);
         if (c->rec)

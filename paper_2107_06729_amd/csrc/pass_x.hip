@@ -74,6 +74,7 @@ hipError_t launch_xinv(hipStream_t s, int LX, int mode, SpecPtr spec, int SX, lo
         const dim3 nb((unsigned)((nrow + R - 1) / R), (unsigned)ph.nb, 1); \
         if (mode == XINV_DEMAG) XI_M(L, R, XINV_DEMAG)                     \
         else if (mode == XINV_HEFF) XI_M(L, R, XINV_HEFF)                  \
+        else if (mode == XINV_UPDATE) XI_M(L, R, XINV_UPDATE)              \
         else XI_M(L, R, XINV_RHS)                                          \
     }
 #define XI(L)                                          \
