@@ -138,105 +138,128 @@ __device__ __forceinline__ void xfwd_tile(const Combo<T>& in, T* __restrict__ mk
         tw2.fetch(twP);
         // stage-0 inputs z[i] = x[2i] + i x[2i+1] of the stage combination,
         // straight from global memory: all loads of one operand are issued
-        // before they are used
-        C v[F::U0][F::R0];
-        long off[F::U0][F::R0];
-        bool ok[F::U0][F::R0];
-        bool two[F::U0][F::R0];
-#pragma unroll
-        for (int m = 0; m < F::U0; ++m) {
-            const int u = threadIdx.x + m * NT;
-#pragma unroll
-            for (int q = 0; q < F::R0; ++q) {
-                int r, i;
-                F::first_input(u, q, r, i);
-                const long g = row0 + r;
-                off[m][q] = g * nin + 2 * i;
-                ok[m][q] = F::live0(u) && g < nrows && 2 * i < nin;
-                two[m][q] = 2 * i + 1 < nin;
-            }
-        }
-        const bool pairs = (nin & 1) == 0;  // rows start 8/16-byte aligned: load both reals at once
-        // every load is issued, from a clamped offset (element 0 for an empty
-        // slot), so a wave keeps all of them in flight; a load under a branch
-        // would be waited for at the branch's end.  Empty slots and the
-        // missing odd element of a row are zeroed after the combination.
-        auto load2 = [&](const T* __restrict__ p, int m, int q) -> C {
-            const long o = ok[m][q] ? off[m][q] : 0;
-            C w;
-            if (pairs) {
-                w = *(const C*)(p + o);
-            } else {
-                w.x = p[o];
-                w.y = p[two[m][q] ? o + 1 : o];
-            }
-            return w;
+        // before they are used.  Addresses are the tile's first real and a 32-bit
+        // offset in bytes (ROWS nin <= 2^15).
+        const int left = (int)(nrows - row0 < ROWS ? nrows - row0 : ROWS);  // rows of the tile
+        const long tile0 = left > 0 ? row0 * nin : 0;
+        auto put_tables = [&] {
+            tw1.put(twl);
+            tw2.put(twp);
         };
-        constexpr int QN = HALF ? (F::R0 + 1) / 2 : F::R0;  // inputs q >= QN lie in the zero half
+        // A wave without a butterfly (fewer than NT of them) goes to the barrier: half of
+        // the waves of a 640-long tile of two rows formed addresses and loaded for
+        // nothing (640x320x4 12.3 -> 11.8 us, 160x80x8 5.0 -> 4.3; with 256-long rows,
+        // where every wave has one, 11.0 both).
+        if (F::U0 > 1 || F::NU0 >= NT || (int)threadIdx.x < F::NU0) {
+            C v[F::U0][F::R0];
+            unsigned off[F::U0][F::R0];
+            bool ok[F::U0][F::R0];
+            bool two[F::U0][F::R0];
 #pragma unroll
-        for (int m = 0; m < F::U0; ++m)
-#pragma unroll
-            for (int q = 0; q < F::R0; ++q) v[m][q] = q < QN ? load2(in.base, m, q) : C{T(0), T(0)};
-        auto add_term = [&](int l) {
-            C w[F::U0][F::R0];
-#pragma unroll
-            for (int m = 0; m < F::U0; ++m)
-#pragma unroll
-                for (int q = 0; q < F::R0; ++q) w[m][q] = q < QN ? load2(in.f[l], m, q) : C{T(0), T(0)};
-            const T cf = in.coef[l];
-#pragma unroll
-            for (int m = 0; m < F::U0; ++m)
+            for (int m = 0; m < F::U0; ++m) {
+                const int u = threadIdx.x + m * NT;
 #pragma unroll
                 for (int q = 0; q < F::R0; ++q) {
-                    v[m][q].x += cf * w[m][q].x;
-                    v[m][q].y += cf * w[m][q].y;
+                    int r, i;
+                    F::first_input(u, q, r, i);
+                    ok[m][q] = F::live0(u) && r < left && 2 * i < nin;
+                    off[m][q] = ok[m][q] ? (__umul24((unsigned)r, (unsigned)nin) + 2 * i) * (unsigned)sizeof(T) : 0;
+                    two[m][q] = 2 * i + 1 < nin;
                 }
-        };
-        if constexpr (STATIC_NF) {
-#pragma unroll
-            for (int l = 0; l < MAX_F; ++l) {
-                if (l >= in.nf) break;
-                add_term(l);
             }
+            const bool pairs = (nin & 1) == 0;  // rows start 8/16-byte aligned: load both reals at once
+            // every load is issued, from a clamped offset (element 0 for an empty
+            // slot), so a wave keeps all of them in flight; a load under a branch
+            // would be waited for at the branch's end.  Empty slots and the
+            // missing odd element of a row are zeroed after the combination.
+            auto load2 = [&](const T* __restrict__ p, int m, int q) -> C {
+                const T* a = (const T*)((const char*)p + off[m][q]);
+                C w;
+                if (pairs) {
+                    w = *(const C*)a;
+                } else {
+                    w.x = a[0];
+                    w.y = a[two[m][q] ? 1 : 0];
+                }
+                return w;
+            };
+            constexpr int QN = HALF ? (F::R0 + 1) / 2 : F::R0;  // inputs q >= QN lie in the zero half
+            const T* base = in.base + tile0;
+#pragma unroll
+            for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                for (int q = 0; q < F::R0; ++q) v[m][q] = q < QN ? load2(base, m, q) : C{T(0), T(0)};
+            auto add_term = [&](int l) {
+                C w[F::U0][F::R0];
+                const T* f = in.f[l] + tile0;
+#pragma unroll
+                for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                    for (int q = 0; q < F::R0; ++q) w[m][q] = q < QN ? load2(f, m, q) : C{T(0), T(0)};
+                const T cf = in.coef[l];
+#pragma unroll
+                for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                    for (int q = 0; q < F::R0; ++q) {
+                        v[m][q].x += cf * w[m][q].x;
+                        v[m][q].y += cf * w[m][q].y;
+                    }
+            };
+            if constexpr (STATIC_NF) {
+#pragma unroll
+                for (int l = 0; l < MAX_F; ++l) {
+                    if (l >= in.nf) break;
+                    add_term(l);
+                }
+            } else {
+                for (int l = 0; l < in.nf; ++l) add_term(l);
+            }
+#pragma unroll
+            for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                for (int q = 0; q < QN; ++q) {
+                    if (!ok[m][q]) v[m][q] = C{T(0), T(0)};
+                    if (!two[m][q]) v[m][q].y = T(0);
+                }
+            if (mk_out) {
+                T* mo = mk_out + tile0;
+#pragma unroll
+                for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                    for (int q = 0; q < QN; ++q)
+                        if (ok[m][q]) {
+                            T* a = (T*)((char*)mo + off[m][q]);
+                            a[0] = v[m][q].x;
+                            if (two[m][q]) a[1] = v[m][q].y;
+                        }
+            }
+#pragma unroll
+            for (int m = 0; m < F::U0; ++m)
+#pragma unroll
+                for (int q = 0; q < QN; ++q) {
+                    v[m][q].x *= fscale;
+                    v[m][q].y *= fscale;
+                }
+            put_tables();
+            F::first_to_lds(v, buf);
         } else {
-            for (int l = 0; l < in.nf; ++l) add_term(l);
+            put_tables();
         }
-#pragma unroll
-        for (int m = 0; m < F::U0; ++m)
-#pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                if (!ok[m][q]) v[m][q] = C{T(0), T(0)};
-                if (!two[m][q]) v[m][q].y = T(0);
-            }
-#pragma unroll
-        for (int m = 0; m < F::U0; ++m)
-#pragma unroll
-            for (int q = 0; q < F::R0; ++q) {
-                if (mk_out && ok[m][q]) {
-                    mk_out[off[m][q]] = v[m][q].x;
-                    if (two[m][q]) mk_out[off[m][q] + 1] = v[m][q].y;
-                }
-                v[m][q].x *= fscale;
-                v[m][q].y *= fscale;
-            }
-        tw1.put(twl);
-        tw2.put(twp);
-        F::first_to_lds(v, buf);
         __syncthreads();
         F::rest(buf, twl);
         // X[k] for k < LX; the lane of k = 0 also writes X[LX], which takes
         // the same z_0 (LX - k and k both wrap to 0)
+        using E = typename Spec<T, S>::elem;
+        E* tile = spec + row0 * (BLK ? SpecBlock<E>::KB : SX);
         for (int e = threadIdx.x; e < ROWS * LX; e += NT) {
             const int r = e / LX, k = e - r * LX;
-            const long g = row0 + r;
-            if (g >= nrows) continue;
+            if (r >= left) continue;
             const C* rb = buf + r * F::RS;
             const C zk = rb[F::P(k)];
             const C zc = cconj(rb[F::P(k == 0 ? 0 : LX - k)]);
             const C ev{(zk.x + zc.x) * T(0.5), (zk.y + zc.y) * T(0.5)};
             const C od{(zk.y - zc.y) * T(0.5), (zc.x - zk.x) * T(0.5)};  // -i (zk - zc)/2
-            using E = typename Spec<T, S>::elem;
-            const SpecRow<BLK, E> out{spec + g * (BLK ? SpecBlock<E>::KB : SX), blk_stride};
+            const SpecRow<BLK, E> out{tile + __umul24((unsigned)r, (unsigned)(BLK ? SpecBlock<E>::KB : SX)), blk_stride};
             out[k] = Spec<T, S>::put(cadd(ev, cmul(od, twp[k])));
             if (k == 0) out[LX] = Spec<T, S>::put(cadd(ev, cmul(od, twp[LX])));
         }
