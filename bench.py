@@ -36,7 +36,7 @@ KIND_PATTERNS = (
     ("zmul", r"k_zmul<float, float,"),
     ("xinv", r"k_xinv<float, float,"),
     ("combine", r"k_combine<float,"),
-    ("extrap", r"k_stage<float>"),
+    ("extrap", r"k_stage<float,"),
     ("final", r"k_stage_final<float,"),
     ("epoly", r"k_epoly<float,|k_stage_ep<float,"),
 )
@@ -63,7 +63,8 @@ def kernel_bytes(n, tsz, p, nnz_comb=1, nnz_final=4, fused_ep=False):
     """Algorithmic HBM bytes per launch of each kernel (one read of every input
     and one write of every output; neighbour reads of M counted once).  With
     fused_ep the Eq. (6) fields are formed by the first extrapolated stage
-    (k_stage_ep, timed as the "epoly" kind)."""
+    (k_stage_ep, timed as the "epoly" kind) and RK4's second last stage writes
+    the sum of Eq. (3) so far in place of its derivative."""
     nx, ny, nz = n
     N = nx * ny * nz
     Px = 2 * nx if nx > 1 else 1
@@ -85,11 +86,13 @@ def kernel_bytes(n, tsz, p, nnz_comb=1, nnz_final=4, fused_ep=False):
         # spectrum + M in; F, G and the next stage input M_2 = M0 + h a F out
         "xinv": sA + vec + 3 * vec,
         "combine": (1 + nnz_comb) * vec + vec,
-        # M_k, one Eq. (6) field and M0 in; F and the next stage input out
-        "extrap": 5 * vec,
+        # M_k, one Eq. (6) field and M0 in; F and the next stage input out; with
+        # the partial sum also F_0 and F_1 in
+        "extrap": (7 if fused_ep else 5) * vec,
         # last sub-step fused with Eq. (3): M_k, its Eq. (6) field, M0 and
-        # F_1..F_{S-1} in; M out (F_S stays in registers)
-        "final": (2 + 1 + (nnz_final - 1)) * vec + vec,
+        # F_1..F_{S-1} in, or the partial sum for the last four; M out (F_S stays
+        # in registers)
+        "final": (2 + (1 if fused_ep else nnz_final)) * vec + vec,
         # Eq. (6) at the distinct sub-step times: p+1 stored fields in, n_times out;
         # fused with the first extrapolated stage: also M_k and M0 in, F and
         # the next stage input out (its own Eq. (6) field is not read back)
@@ -112,6 +115,9 @@ def batch_step_bytes(problems, tsz, p, fused_ep=True):
         nx, ny, nz = n
         kx = (nx + 1 if nx > 1 else 1)
         kern = 6 * kx * ((ny + 1) if ny > 1 else 1) * ((nz + 1) if nz > 1 else 1) * tsz
+        if fused_ep and nz <= 4:
+            # one kernel for the y and z passes: spectrum A in and out
+            kb.update(yfwd=0, yinv=0, zmul=2 * (kb["xfwd"] - 3 * nx * ny * nz * tsz) + kern)
         per = kb["xfwd"] + kb["yfwd"] + kb["zmul"] + kb["yinv"] + kb["xinv"] + kb["epoly"] \
             + (1 if fused_ep else 2) * kb["extrap"] + kb["final"]
         total += nb * (per - kern) + kern
