@@ -342,8 +342,8 @@ llgx_status llgx_batch_info(llgx_batch b, int32_t* ngroups, int64_t* total_cells
  *     captures a step and frees in llgx_batch_destroy.  Steps that have no
  *     job-table form (16-bit spectra, padded lengths above 1024 along x,
  *     512 along y or 64 along z) are captured as with LLGX_BATCH_STREAMS.
- *   LLGX_BATCH_STREAMS (default): each group's own launches, on streams
- *     forked from the batch stream inside the captured graph, so the
+ *   LLGX_BATCH_STREAMS (default): each group's own launches and graphs, on
+ *     streams forked from the batch stream for the whole call, so the
  *     kernels of different meshes overlap, and a small mesh's step does not
  *     wait at every pass for the large ones (the faster of the two on the
  *     64-sample sweep of four meshes).

@@ -75,8 +75,10 @@ struct GraphKey {
     int method, p;
     long gen;
     int nsteps = 1;
+    int renorm = 0;  // single handles' graphs hold the renormalisations too
     bool operator<(const GraphKey& o) const {
         if (nsteps != o.nsteps) return nsteps < o.nsteps;
+        if (renorm != o.renorm) return renorm < o.renorm;
         if (M != o.M) return M < o.M;
         if (slot0 != o.slot0) return slot0 < o.slot0;
         if (hist_slots != o.hist_slots) return hist_slots < o.hist_slots;
@@ -1301,7 +1303,7 @@ static llgx_status do_run_fixed(Ctx* c, const llgx_stepper* s, int64_t nsteps, i
         // a steady, uniform step is followed by steady, uniform steps: the
         // next `nb` steps are one graph
         const int nb = nsteps - i >= GRAPH_BLOCK_STEPS ? GRAPH_BLOCK_STEPS : 1;
-        GraphKey key{c->M, free_slot(c), {}, s->h, s->method, p, c->kernel_gen, nb};
+        GraphKey key{c->M, free_slot(c), {}, s->h, s->method, p, c->kernel_gen, nb, s->renormalize != 0};
         for (auto& hh : c->hist) key.hist_slots.push_back(hh.slot);
         auto it = c->graphs.find(key);
         if (it == c->graphs.end()) {
@@ -1769,9 +1771,8 @@ struct Batch {
     hipStream_t stream = nullptr;
     std::string err;
     std::map<std::vector<GraphKey>, hipGraphExec_t> graphs;
-    // groups 1.. get streams of their own (default priority) inside a captured
-    // step, forked from and joined back into `stream`, so meshes of different
-    // shapes run side by side
+    // groups 1.. get streams of their own (default priority), forked from and joined
+    // back into `stream`, so meshes of different shapes run side by side
     std::vector<hipStream_t> gstreams;
     std::vector<hipEvent_t> joins;
     hipEvent_t fork = nullptr;
@@ -1786,7 +1787,7 @@ struct Batch {
     int last_jobs = 0, last_kernels = 0;
 };
 
-// the streams and events of forked captures: ng - 1 side streams (default
+// the streams and events of forked steps: ng - 1 side streams (default
 // priority) and their join events, and the fork event
 static llgx_status fork_streams(Batch* bt, size_t ng) {
     if (ng < 2 || !bt->gstreams.empty()) return LLGX_OK;
@@ -1807,10 +1808,9 @@ static llgx_status fork_streams(Batch* bt, size_t ng) {
 }
 
 // While on, the groups after the first step on the side streams, forked from the
-// batch stream once and joined back by end() or on the way out.  The steps of a run
-// that are not replayed (the first p of an extrapolated one) then overlap as the
-// captured ones do (32 samples on four meshes, the first 4 steps of RK4 p = 4:
-// 3.13 ms one group after another, 2.41 so).
+// batch stream once and joined back by end() or on the way out, so the small meshes'
+// launches fill what the largest one's leave idle (32 samples on four meshes, the
+// first 4 steps of RK4 p = 4: 3.13 ms one group after another, 2.41 so).
 struct Forked {
     Batch* bt;
     bool on = false;
@@ -1818,7 +1818,7 @@ struct Forked {
     ~Forked() { (void)end(); }
     llgx_status begin() {
         const size_t ng = bt->groups.size();
-        if (on || ng < 2 || !bt->stream || bt->mode != LLGX_BATCH_STREAMS) return LLGX_OK;
+        if (on || ng < 2 || !bt->stream) return LLGX_OK;
         for (const Ctx* c : bt->groups)
             if (c->prof) return LLGX_OK;  // launches are timed one after another
         if (llgx_status st = fork_streams(bt, ng)) return st;
@@ -2105,6 +2105,29 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
     return LLGX_OK;
 }
 
+// Fixed steps of every group on its own stream, each replayed from the group's own
+// one-step graphs as a single handle's are.  The groups' launches are enqueued
+// GROUP_STEPS steps at a time in turn, so all streams have work, and fewer than
+// GRAPH_BLOCK_STEPS, since the time between two graphs of one group is filled by the
+// others' work.  One graph of all groups per step waited for the largest mesh at each
+// step's end: 32 samples on four meshes 324 us a step (RK4 p = 4), 292 so.
+constexpr int GROUP_STEPS = 4;
+
+template <typename T>
+static llgx_status run_groups(Batch* bt, const llgx_stepper* s, int64_t nsteps, int use_graph) {
+    Forked forked(bt);
+    if (llgx_status st = forked.begin()) return st;
+    for (int64_t i = 0; i < nsteps; i += GROUP_STEPS)
+        for (Ctx* c : bt->groups)
+            if (llgx_status st = do_run_fixed<T>(c, s, std::min<int64_t>(GROUP_STEPS, nsteps - i), use_graph, nullptr)) {
+                bt->err = c->err;
+                return st;
+            }
+    bt->last_jobs = 0;
+    bt->last_kernels = -1;
+    return forked.end();
+}
+
 template <typename T>
 static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nsteps, int use_graph) {
     if (!s || s->adaptive) {
@@ -2115,7 +2138,7 @@ static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nst
         bt->err = "ABM2 is stepped per handle, not in batches";
         return LLGX_E_UNSUPPORTED;
     }
-    Forked forked(bt);
+    if (bt->mode == LLGX_BATCH_STREAMS) return run_groups<T>(bt, s, nsteps, use_graph);
     for (int64_t i = 0; i < nsteps; ++i) {
         bool steady = use_graph && bt->stream != nullptr;
         std::vector<Plan> plans(bt->groups.size());
@@ -2149,7 +2172,6 @@ static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nst
             for (auto& hh : c->hist) key.hist_slots.push_back(hh.slot);
             keys.push_back(key);
         }
-        if (llgx_status st = steady ? forked.end() : forked.begin()) return st;
         if (!steady) {
             for (Ctx* c : bt->groups) {
                 llgx_status st = do_step<T>(c, s, nullptr);
@@ -2161,65 +2183,15 @@ static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nst
             continue;
         }
         auto it = bt->graphs.find(keys);
-        if (it == bt->graphs.end() && bt->mode == LLGX_BATCH_JOBS) {
+        if (it == bt->graphs.end()) {
             hipGraphExec_t ge;
             int nk = 0;
             llgx_status st = capture_jobs<T>(bt, plans, &ge, &nk);
-            if (st == LLGX_OK) {
-                it = bt->graphs.emplace(keys, ge).first;
-                bt->last_jobs = 1;
-                bt->last_kernels = nk;
-            } else if (st != LLGX_E_UNSUPPORTED) {
-                return st;
-            }
-        }
-        if (it == bt->graphs.end()) {
-            hipGraph_t gr;
-            if (hipStreamBeginCapture(bt->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-                bt->err = "graph capture could not start";
-                return LLGX_E_HIP;
-            }
-            const size_t ng = bt->groups.size();
-            llgx_status st = fork_streams(bt, ng);
-            if (st == LLGX_OK && ng > 1 && hipEventRecord(bt->fork, bt->stream) != hipSuccess)
-                st = LLGX_E_HIP, bt->err = "event record failed";
-            for (size_t g = 0; g < ng && st == LLGX_OK; ++g) {
-                Ctx* c = bt->groups[g];
-                if (g > 0) {
-                    if (hipStreamWaitEvent(bt->gstreams[g - 1], bt->fork, 0) != hipSuccess) {
-                        st = LLGX_E_HIP;
-                        bt->err = "stream wait failed";
-                        break;
-                    }
-                    c->stream = bt->gstreams[g - 1];
-                }
-                st = enqueue_attempt<T>(c, plans[g]);
-                if (st) bt->err = c->err;
-                if (g > 0) {
-                    if (st == LLGX_OK && hipEventRecord(bt->joins[g - 1], c->stream) != hipSuccess)
-                        st = LLGX_E_HIP, bt->err = "event record failed";
-                    c->stream = bt->stream;
-                }
-            }
-            for (size_t g = 1; g < ng && st == LLGX_OK; ++g)
-                if (hipStreamWaitEvent(bt->stream, bt->joins[g - 1], 0) != hipSuccess)
-                    st = LLGX_E_HIP, bt->err = "stream wait failed";
-            hipError_t e2 = hipStreamEndCapture(bt->stream, &gr);
+            if (st == LLGX_E_UNSUPPORTED) return run_groups<T>(bt, s, nsteps - i, use_graph);
             if (st) return st;
-            if (e2 != hipSuccess) {
-                bt->err = std::string("graph capture failed: ") + hipGetErrorString(e2);
-                return LLGX_E_HIP;
-            }
-            hipGraphExec_t ge;
-            if (hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0) != hipSuccess) {
-                (void)hipGraphDestroy(gr);
-                bt->err = "graph instantiation failed";
-                return LLGX_E_HIP;
-            }
-            (void)hipGraphDestroy(gr);
             it = bt->graphs.emplace(keys, ge).first;
-            bt->last_jobs = 0;
-            bt->last_kernels = -1;
+            bt->last_jobs = 1;
+            bt->last_kernels = nk;
         }
         if (hipGraphLaunch(it->second, bt->stream) != hipSuccess) {
             bt->err = "graph launch failed";
@@ -2239,7 +2211,7 @@ static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nst
             c->h_next = s->h;
         }
     }
-    return forked.end();
+    return LLGX_OK;
 }
 
 }  // namespace llgx

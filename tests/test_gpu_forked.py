@@ -37,3 +37,23 @@ def test_forked_eager_steps_equal_serial(method, extrap, graph, renormalize):
         bt.close()
     for a, b in zip(*got):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def test_renormalised_steps_do_not_replay_plain_ones():
+    """Graphs of steps with and without renormalisation are different ones."""
+    import torch
+
+    from tests.gpu_util import sim
+    import paper_2107_06729_amd as llgx
+    n = (40, 24, 2)
+    s = sim(film(n, CELL), "f64", stream=torch.cuda.Stream())
+    s.set_m(to_dev(workloads.random_m(n, 8e5, 70), "f64"))
+    plain = llgx.make_stepper("HEUN", extrap=1, h=2e-13)
+    renorm = llgx.make_stepper("HEUN", extrap=1, h=2e-13, renormalize=True)
+
+    def drift():
+        return float(np.abs(np.sqrt((to_host(s.get_m()) ** 2).sum(axis=0)) / 8e5 - 1.0).max())
+    s.run_fixed(plain, 12)
+    assert drift() > 1e-9
+    s.run_fixed(renorm, 12)
+    assert drift() < 1e-14
