@@ -230,10 +230,13 @@ llgx_status llgx_run(llgx_handle h, const llgx_stepper* s, double t_end, double 
                             same kernel                                      */
 #define LLGX_K_YINV 3    /* inverse y pass (not on thin meshes, see ZMUL)     */
 #define LLGX_K_XINV 4    /* inverse x pass fused with H_eff and the LLG RHS   */
-#define LLGX_K_COMBINE 5 /* stage input M_k = M0 + h sum b F (Eq. 4)          */
-#define LLGX_K_EXTRAP 6  /* Eq. (6) sub-step field + H_eff + LLG RHS          */
+#define LLGX_K_COMBINE 5 /* stage input M_k = M0 + h sum b F (Eq. 4) where no
+                            other kernel writes it                           */
+#define LLGX_K_EXTRAP 6  /* Eq. (6) sub-step field + H_eff + LLG RHS, with the
+                            next stage input                                 */
 #define LLGX_K_FINAL 7   /* Eq. (3) update and error-norm partials (fused with
-                            the last sub-step when it is extrapolated)       */
+                            the last sub-step when it is extrapolated; full
+                            fixed steps take the update in XINV)             */
 #define LLGX_K_EPOLY 8   /* Eq. (6) fields for every distinct sub-step time   */
 #define LLGX_K_OTHER 9   /* reductions, renormalisation                       */
 #define LLGX_K_COUNT 10

@@ -8,11 +8,13 @@
 //                      time t_j of the tableau: one pass over the p+1 stored
 //                      fields serves all stages                          (Eq. 6)
 // * stage_block      : H_d = sum_i w_i g_i - N00 M_k (g: stored or E
-//                      fields), H_eff and the LLG right-hand side        (Eq. 6, 1)
+//                      fields), H_eff and the LLG right-hand side        (Eq. 6, 1),
+//                      with the next stage input of Eq. (4)
 // * stage_final_block: the last sub-step fused with M = M0 + h sum c_k F_k
 //                      and the per-cell error |h sum (c_k - c^_k) F_k| / Ms (Eq. 3)
 // * stage_ep_block   : the first extrapolated sub-step fused with Eq. (6) at
 //                      every distinct sub-step time                     (Eq. 6, 1)
+// * predicted_block  : ABM2's sub-step at the predicted state            (Eq. 6, 1)
 // * final_blocks     : Eq. (3) update and error when the last stage is exact
 #pragma once
 #include <hip/hip_runtime.h>

@@ -1,6 +1,6 @@
 // Streaming kernels of one explicit step (Eq. (3)-(4)) and of the
 // extrapolated sub-steps (Eq. (6)), for gfx950.  The per-block work of the
-// first five is in cells.hpp (shared with the job-table batched kernels);
+// first seven is in cells.hpp (shared with the job-table batched kernels);
 // here are the kernels over their own grids and the launchers.
 //
 // * k_combine    : M_k = M0 + sum_l (h b_kl) F_l                        (Eq. 4)
@@ -8,7 +8,9 @@
 //                  t_j of the tableau: one pass over the p+1 stored fields
 //                  serves all stages                                     (Eq. 6)
 // * k_stage      : H_d = sum_i w_i g_i - N00 M_k (g: stored or E fields),
-//                  H_eff and the LLG right-hand side at a sub-step      (Eq. 6, 1)
+//                  H_eff and the LLG right-hand side at a sub-step      (Eq. 6, 1),
+//                  with the next stage input of Eq. (4)
+// * k_predicted  : ABM2's sub-step at the predicted state               (Eq. 6, 1)
 // * k_stage_ep   : k_stage of the first extrapolated sub-step fused with
 //                  k_epoly (the stored fields read once, no read-back of
 //                  its own Eq. (6) field)                               (Eq. 6, 1)
@@ -18,8 +20,8 @@
 // * k_renorm, k_mean, k_cast, reductions.
 // Per-cell kernels run on a 2-D grid (x along threads, rows of the mesh
 // along blocks) so cell coordinates need no divisions.  Reductions write
-// per-block partials with vector stores and are finished by one block (no
-// atomics, deterministic order).
+// per-block partials with vector stores and are finished by one block or, the
+// error norm's, on the host (no atomics, deterministic order).
 #include <hip/hip_runtime.h>
 
 #include <cmath>

@@ -6,8 +6,9 @@ namespace llgx {
 // Threads of a tile.  Variant 0 gives every stage whole rounds: 3 nz LY/8
 // radix-8 butterflies against LY product units.  Above 512 threads a second
 // tile no longer fits beside the first (registers), and the last columns of
-// an odd Kx run alone: 256x256x4 FP32 17.7 us with 768 threads, 14.3 with 512.
-// Variants 1 and 2 (half of LY, LY) are the faster ones on some shapes
+// an odd Kx run alone: 256x256x4 FP32 17.7 us with 768 threads, 14.3 with 512
+// (13.5 with the rows' present padding).  Variants 1 and 2 (half of LY, LY) are the
+// faster ones on some shapes
 // (512x512x2 FP64 57.0 against 57.3, 1000x100x4 FP32 17.0 against 20.0).
 constexpr int yzy_nth(int LY, int nz, int v) {
     const int n = v == 1 ? LY / 2 : v == 2 ? LY : nz == 1 ? LY / 2 : nz == 2 ? LY : LY * 3 * nz / 8;
@@ -18,12 +19,12 @@ constexpr int yzy_nth(int LY, int nz, int v) {
 // The fused pass takes every thin mesh whose one-column tile fits a CU's LDS
 // with room for the tile's launch beside it.  Microseconds of the y, z and y
 // passes with their default tiles against this one, back to back:
-//   60x60x1 FP32 10.1 / 4.2, 256x64x1 FP32 9.9 / 4.3, 32x32x2 FP64 8.7 / 3.9,
-//   128x128x4 FP32 12.6 / 6.6, 256x256x4 FP32 23.1 / 14.3 and FP64 35.6 / 30.5,
-//   512x512x1 FP32 28.5 / 13.4, 300x512x4 FP32 69 / 59, 1000x1000x2 FP32 178 / 99,
-//   7x1000x2 FP32 26 / 18.
+//   60x60x1 FP32 10.1 / 3.9, 256x64x1 FP32 9.9 / 3.9, 32x32x2 FP64 8.7 / 3.9,
+//   128x128x4 FP32 12.6 / 6.5, 256x256x4 FP32 23.1 / 13.5 and FP64 35.6 / 28.1,
+//   512x512x1 FP32 28.5 / 12.0, 1000x1000x2 FP32 178 / 92, 7x1000x2 FP32 26 / 18,
+//   300x512x4 FP32 69 / 59 at Px = 1024 (37 at the shorter Px it takes now).
 // On the largest tiles (110 KB: one workgroup a CU) the separate passes come
-// level once autotuned (300x512x4: 58), so larger ones are not taken.
+// level once autotuned (300x512x4 at Px = 1024: 58), so larger ones are not taken.
 template <typename T>
 bool yzy_ok(int LY, int nz) {
     return LY >= 2 && LY <= MAX_LEN && nz >= 1 && nz <= YZY_MAX_NZ && yzy_lds<T>(LY, nz, 1) <= YZY_LDS_MAX;

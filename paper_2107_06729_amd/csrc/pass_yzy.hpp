@@ -5,8 +5,8 @@
 // Bound: on these meshes the three separate passes are short kernels that
 // move spectrum B (twice the rows of A) out and in, with z tiles of a few KB;
 // one kernel reads and writes A once and the folded kernel once.  What is
-// left is the vector arithmetic (about 1.7 k instructions a wave at 256x256x4,
-// 5.8 us of the 14.3 us at full issue), the LDS passes between the stages (3
+// left is the vector arithmetic (1.26 k instructions a wave at 256x256x4,
+// 4.2 us of the 13.5 us at full issue), the LDS passes between the stages (3
 // us) and the latency of the first loads, which one tile a CU cannot hide.  On
 // small meshes it is the launches: three kernels an evaluation instead of
 // five (figures at yzy_ok).
