@@ -226,8 +226,8 @@ llgx_status llgx_run(llgx_handle h, const llgx_stepper* s, double t_end, double 
 #define LLGX_K_XFWD 0    /* stage combination + forward real-to-complex x pass */
 #define LLGX_K_YFWD 1    /* forward y pass (not on thin meshes, see ZMUL)     */
 #define LLGX_K_ZMUL 2    /* z forward, k-space tensor product, z inverse; on
-                            thin meshes (nz <= 4) with both y passes in the
-                            same kernel                                      */
+                            thin meshes (nz <= 4, FP32 spectra up to 8) with
+                            both y passes in the same kernel                 */
 #define LLGX_K_YINV 3    /* inverse y pass (not on thin meshes, see ZMUL)     */
 #define LLGX_K_XINV 4    /* inverse x pass fused with H_eff and the LLG RHS   */
 #define LLGX_K_COMBINE 5 /* stage input M_k = M0 + h sum b F (Eq. 4) where no
@@ -257,7 +257,8 @@ llgx_status llgx_profile_read(llgx_handle h, double ms[LLGX_K_COUNT], int64_t la
  * under the key (precision, spectral storage, mesh, sample count), so handles
  * created later with that key start with it.  us_out (may be NULL) receives
  * the chosen variants' fastest-round microseconds per launch (0 for a pass
- * the mesh does not need).  Needs llgx_precompute_demag and llgx_set_m (LLGX_E_STATE);
+ * the mesh does not need; on thin meshes the y passes are those of job-table
+ * steps).  Needs llgx_precompute_demag and llgx_set_m (LLGX_E_STATE);
  * uses only the spectral workspace and the stage scratch array, so the
  * stepping state is unchanged.  Synchronises.
  * llgx_time_passes: the same measurement for the current variants only.

@@ -150,9 +150,12 @@ hipError_t launch_zmul(hipStream_t s, int LZ, SpecPtr buf, int SX, int Kx, int n
 template <typename T, typename S>
 hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int Kx, int ny, int nz, int nb,
                       const T* kcol, int KYS, const cx<T>* tw, T yscale, int variant);
-// whether the fused pass takes a mesh of nz cells padded to LY along y
+// whether the fused pass takes a mesh of nz cells padded to LY along y (native:
+// spectra stored in the working precision)
 template <typename T>
-bool yzy_ok(int LY, int nz);
+bool yzy_ok(int LY, int nz, bool native);
+// its variant on a new handle, for so many columns (all samples)
+int yzy_default(int LY, int nz, long columns);
 hipError_t launch_newell_octant(hipStream_t s, int nx, int ny, int nz, double dx, double dy, double dz,
                                 double* octant);
 hipError_t launch_scatter_tensor(hipStream_t s, const double* octant, int comp, int nx, int ny, int nz,

@@ -389,6 +389,12 @@ static bool pass_exists(const Ctx* c, int kind) {
     return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && (c->Py == 1 || fused_yz(c)));
 }
 
+// passes that are timed and tuned: thin meshes' separate y passes too, which
+// job-table steps launch
+static bool pass_timed(const Ctx* c, int kind) {
+    return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && c->Py == 1);
+}
+
 // launch one pass (kind LLGX_K_XFWD .. LLGX_K_XINV) with the handle's variant
 template <typename T, typename S>
 static llgx_status run_pass(Ctx* c, int kind, const EvalArgs<T>& a) {
@@ -1523,7 +1529,7 @@ static std::string tune_key(const Ctx* c) {
 //     line lose (15.2 / 16.3).
 //   z pass: double tiles up to length 8 and at 24 (600x520x4 36.3 / 30.0, 300x300x12
 //     28.8 / 27.1), FP64 up to 16 (400x400x6 85.9 / 68.7); half ones for FP64 64
-//     (128x128x32 27.3 / 24.5).  The fused pass of thin meshes keeps its variant 0.
+//     (128x128x32 27.3 / 24.5).  The fused pass of thin meshes: yzy_default.
 static void default_variants(Ctx* c) {
     const bool f32 = c->prec == LLGX_F32, native = c->spectral == LLGX_SPEC_NATIVE;
     const long rows = 3L * c->ny * c->nz * c->nb, mesh_rows = (long)c->ny * c->nz * c->nb;
@@ -1541,6 +1547,7 @@ static void default_variants(Ctx* c) {
     c->var[LLGX_K_XINV] = f32 || xi < 1024 ? 1 : 0;
     const int ylow = f32 ? 320 : 256;
     c->var[LLGX_K_YFWD] = c->var[LLGX_K_YINV] = native && c->Py >= ylow && c->Py <= 512 ? 1 : 0;
+    if (c->thin) c->var[LLGX_K_ZMUL] = yzy_default(c->Py, c->nz, (long)c->Kx * c->nb);
     if (!c->thin) c->var[LLGX_K_ZMUL] = c->Pz <= 8 || c->Pz == 24 || (!f32 && c->Pz == 16) ? 2 : !f32 && c->Pz == 64 ? 1 : 0;
 }
 
@@ -1572,7 +1579,7 @@ static llgx_status tune_ctx(Ctx* c, int reps, double us_out[5]) {
     for (int k = 0; k < 5; ++k) {
         te.var[k] = 0;
         te.us[k] = 0.0;
-        if (!pass_exists(c, k)) continue;
+        if (!pass_timed(c, k)) continue;
         // the variants take turns over kTuneRounds rounds and each keeps its
         // fastest round, so a clock ramp or a burst of other work during one
         // variant's measurement does not decide the choice
@@ -1667,7 +1674,7 @@ static llgx_status create_ctx(const llgx_problem* p, int nb, const double* ha_li
     c->Kzf = c->Pz > 1 ? c->Pz / 2 + 1 : 1;
     c->KYS = (c->Kyf + 7) / 8 * 8;
     c->thin = c->LX > 0 && c->Py > 1 &&
-              (precision == LLGX_F32 ? yzy_ok<float>(c->Py, c->nz) : yzy_ok<double>(c->Py, c->nz));
+              (precision == LLGX_F32 ? yzy_ok<float>(c->Py, c->nz, mixed) : yzy_ok<double>(c->Py, c->nz, mixed));
     const size_t cbytes = spectral == LLGX_SPEC_NATIVE ? 2 * c->tsz : 4;  // bytes per stored complex value
     const size_t vbytes = 3 * (size_t)c->ncell * nb * c->tsz;
     llgx_status st = LLGX_OK;
@@ -2634,7 +2641,7 @@ llgx_status llgx_time_passes(llgx_handle h, int32_t reps, double us_out[5]) {
     if (!c->have_m) return c->fail(LLGX_E_STATE, "magnetization not set (llgx_set_m)");
     for (int k = 0; k < 5; ++k) {
         us_out[k] = 0.0;
-        if (!pass_exists(c, k)) continue;
+        if (!pass_timed(c, k)) continue;
         llgx_status st = time_pass_any(c, k, c->var[k], reps, &us_out[k]);
         if (st) return st;
     }

@@ -25,14 +25,28 @@ constexpr int yzy_nth(int LY, int nz, int v) {
 //   300x512x4 FP32 69 / 59 at Px = 1024 (37 at the shorter Px it takes now).
 // On the largest tiles (110 KB: one workgroup a CU) the separate passes come
 // level once autotuned (300x512x4 at Px = 1024: 58), so larger ones are not taken.
+// Meshes of 5 to 8 layers, FP32 spectra only (a thread's three z lines take about 200
+// registers; FP64 ones do not fit, and 16-bit spectra keep the order of the separate
+// passes): 21x13x5 10.2 / 5.9, 60x60x8 11.0 / 7.8, 160x80x8 15.6 / 9.0, 128x128x8
+// 14.8 / 11.1, 200x120x6 18.4 / 13.0, 256x256x5 24.8 / 19.3, 300x200x7 31.6 / 27.8,
+// 640x320x6 (95 KiB) level, and 256x256x8 (106 KiB) 30.6 / 32.9: the line is at 96.
 template <typename T>
-bool yzy_ok(int LY, int nz) {
-    return LY >= 2 && LY <= MAX_LEN && nz >= 1 && nz <= YZY_MAX_NZ && yzy_lds<T>(LY, nz, 1) <= YZY_LDS_MAX;
+bool yzy_ok(int LY, int nz, bool native) {
+    if (nz > 4 && !(native && sizeof(T) == 4)) return false;
+    return LY >= 2 && LY <= MAX_LEN && nz >= 1 && nz <= YZY_MAX_NZ && yzy_lds<T>(LY, nz, 1) <= yzy_lds_max(nz);
 }
 #if LLGX_INST == 0
-template bool yzy_ok<float>(int, int);
+// Variant 0, but with 5 to 8 layers, more columns than CUs and two tiles in a CU's
+// LDS fewer threads, so that two tiles fit its registers as well (us: 200x120x6 17.8
+// / 13.0, 256x250x5 23.6 / 19.5, 400x128x8 29.6 / 23.9; one column a CU the other way,
+// 128x128x8 11.2 / 11.6, and so tiles that are alone in the LDS, 300x200x7 28.7 / 39.1).
+int yzy_default(int LY, int nz, long columns) {
+    if (nz <= 4 || columns <= 256 || yzy_lds<float>(LY, nz, 1) > 80 * 1024) return 0;
+    return LY <= 256 ? 2 : 1;
+}
+template bool yzy_ok<float>(int, int, bool);
 #elif LLGX_INST == 3
-template bool yzy_ok<double>(int, int);
+template bool yzy_ok<double>(int, int, bool);
 #endif
 
 template <typename T, typename S>
@@ -47,7 +61,7 @@ hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int 
         sp, blk_stride, Kx, ny, kcol, KYS, tw, yscale)
 #define YZ_N(LL, NZ)                                          \
     case NZ:                                                  \
-        if constexpr (yzy_lds<T>(LL, NZ, 1) <= YZY_LDS_MAX) { \
+        if constexpr (yzy_lds<T>(LL, NZ, 1) <= yzy_lds_max(NZ)) { \
             if (variant == 0)                                 \
                 YZ_L(LL, NZ, 0);                              \
             else if (variant == 1)                            \
@@ -57,10 +71,15 @@ hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int 
             return hipGetLastError();                         \
         }                                                     \
         return hipErrorInvalidValue;
+#if LLGX_INST == 0
+#define YZ_16(LL) YZ_N(LL, 5) YZ_N(LL, 6) YZ_N(LL, 7) YZ_N(LL, 8)
+#else
+#define YZ_16(LL)
+#endif
 #define YZ(LL)                                             \
     case LL:                                               \
         switch (nz) {                                      \
-            YZ_N(LL, 1) YZ_N(LL, 2) YZ_N(LL, 3) YZ_N(LL, 4) \
+            YZ_N(LL, 1) YZ_N(LL, 2) YZ_N(LL, 3) YZ_N(LL, 4) YZ_16(LL) \
             default:                                       \
                 return hipErrorInvalidValue;               \
         }
@@ -71,6 +90,7 @@ hipError_t launch_yzy(hipStream_t s, int LY, SpecPtr spec, long blk_stride, int 
     }
 #undef YZ
 #undef YZ_N
+#undef YZ_16
 #undef YZ_L
 }
 

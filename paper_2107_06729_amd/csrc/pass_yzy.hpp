@@ -1,4 +1,4 @@
-// The y and z work of Eq. (2) for thin meshes (nz <= 4) in one kernel: y
+// The y and z work of Eq. (2) for thin meshes (nz <= 4, FP32 <= 8) in one kernel: y
 // forward, z forward, k-space product, z inverse, y inverse of TK columns kx,
 // every row and every component of them in LDS.
 //
@@ -25,6 +25,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "fft_passes.hpp"
 #include "fft_row.hpp"
 #include "kernels.hpp"
 #include "spec_store.hpp"
@@ -32,10 +33,59 @@
 
 namespace llgx {
 
-constexpr int YZY_MAX_NZ = 4;
+constexpr int YZY_MAX_NZ = 8;
 
-// z transform length of nz cells: 1, 4, 8, 8
-constexpr int yzy_lz(int nz) { return nz == 1 ? 1 : nz == 2 ? 4 : 8; }
+// z transform length of nz cells: 1, 4, 8, 8, then 16
+constexpr int yzy_lz(int nz) { return nz == 1 ? 1 : nz == 2 ? 4 : nz <= 4 ? 8 : 16; }
+
+// cos(z pi / 8) as the twiddle tables hold it; -sin is the value four places on
+template <typename T>
+__device__ __forceinline__ constexpr T cos16(int z) {
+    constexpr double c[12] = {1.0, 0.92387953251128675613, 0.70710678118654752440, 0.38268343236508977173,
+                              6.123233995736766e-17, -0.38268343236508977173, -0.70710678118654752440, -0.92387953251128675613,
+                              -1.0, -0.92387953251128675613, -0.70710678118654752440, -0.38268343236508977173};
+    return (T)c[z];
+}
+
+// z forward, product and z inverse of one (column, ky) with nz = 5 to 8 cells: 16
+// outputs as two transforms of 8 over the cells, kz even and odd (the first stage of
+// two, the other half of whose inputs is the padding, leaves the cells as they are)
+template <typename T, int NZ>
+__device__ __forceinline__ void yzy_z16(const T (&k)[9][6], bool yneg, cx<T> (&x)[3][8]) {
+    using C = cx<T>;
+    C out[3][8];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        C w[3][8];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int z = 0; z < 8; ++z)
+                w[a][z] = j == 0 || z == 0 ? x[a][z] : cmul(x[a][z], C{cos16<T>(z), cos16<T>(z + 4)});
+            dft_r<8, false>(w[a]);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int kz = j + 2 * r;
+            apply_kernel(k[kz <= 8 ? kz : 16 - kz], yneg, kz > 8, w[0][r], w[1][r], w[2][r]);
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            dft_r<8, true>(w[a]);
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) {
+                if (j == 0)
+                    out[a][z] = w[a][z];
+                else
+                    out[a][z] = cadd(out[a][z], z == 0 ? w[a][z] : cmulc(w[a][z], C{cos16<T>(z), cos16<T>(z + 4)}));
+            }
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int z = 0; z < NZ; ++z) x[a][z] = out[a][z];
+}
 
 template <typename T, int LY, int NZ, int TK, int NTH>
 struct YzyShared {
@@ -50,7 +100,7 @@ template <typename T>
 constexpr long yzy_lds(int LY, int nz, int tk) {
     return (3L * nz * tk * (LY + ((LY & (LY - 1)) == 0 ? LY / (sizeof(T) == 4 ? 16 : 8) : 0) + 1) + LY) * 2 * (long)sizeof(T);
 }
-constexpr long YZY_LDS_MAX = 128 * 1024;
+constexpr long yzy_lds_max(int nz) { return (nz <= 4 ? 128 : 96) * 1024; }
 
 template <typename T, typename S, int LY, int NZ, int TK, int NTH>
 __global__ __launch_bounds__(NTH) void k_yzy(typename Spec<T, S>::elem* __restrict__ spec, long blk_stride, int Kx,
@@ -127,6 +177,20 @@ __global__ __launch_bounds__(NTH) void k_yzy(typename Spec<T, S>::elem* __restri
         const int c = u / LY, ky = u - c * LY;
         const bool yneg = 2 * ky > LY;
         C* col = buf + c * Ff::RS + Ff::P(ky);
+        if constexpr (LZ == 16) {
+            C x[3][8];
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int z = 0; z < 8; ++z)
+                    x[a][z] = z < NZ ? col[(a * NZ + z) * TK * Ff::RS] : C{T(0), T(0)};
+            yzy_z16<T, NZ>(k, yneg, x);
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int z = 0; z < NZ; ++z) col[(a * NZ + z) * TK * Ff::RS] = x[a][z];
+            continue;
+        }
         C v[3][LZ];
 #pragma unroll
         for (int a = 0; a < 3; ++a)
