@@ -2130,8 +2130,10 @@ static llgx_status run_groups(Batch* bt, const llgx_stepper* s, int64_t nsteps, 
                 bt->err = c->err;
                 return st;
             }
-    bt->last_jobs = 0;
-    bt->last_kernels = -1;
+    if (use_graph && !bt->groups[0]->graphs.empty()) {
+        bt->last_jobs = 0;
+        bt->last_kernels = -1;
+    }
     return forked.end();
 }
 
