@@ -132,7 +132,8 @@ struct Ctx {
     double* err_dev = nullptr;  // steps, ERR_SLOTS), their device address, and how many of them the
     int err_n = 0;              // latest attempt writes
     int* empty_flag = nullptr;  // device: [0] some cell of M has M = 0; [1] always 1
-    bool empty_stale = false;   // M changed since the flag was set (batches: see check_stepper)
+    bool empty_stale = false;   // M changed and nobody looked yet (batches: see note_new_state)
+    bool look_captured = false; // a look is in a graph of the caller's, which may run at any time
     // during a field call: flag [1], so every neighbour is tested (the same result;
     // a look at the input first was two launches, a third of a small mesh's call)
     bool field_input = false;
@@ -309,15 +310,39 @@ static Combo<T> plain(const void* base) {
     return cb;
 }
 
+static llgx_status capturing(Ctx* c, bool* yes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->stream) HIPCHK(c, hipStreamIsCapturing(c->stream, &cap));
+    *yes = cap != hipStreamCaptureStatusNone;
+    return LLGX_OK;
+}
+
 // Recompute the empty-cell flag of the state M on the stream, with no host
 // synchronisation.
 static llgx_status detect_empty(Ctx* c) {
+    bool cap = false;
+    if (llgx_status st = capturing(c, &cap)) return st;
     HIPCHK(c, launch_fill_int(c->stream, c->empty_flag, 1, 0));
     if (c->prec == LLGX_F32)
         HIPCHK(c, launch_detect_empty<float>(c->stream, c->ncell, c->nb, (const float*)c->M, c->empty_flag));
     else
         HIPCHK(c, launch_detect_empty<double>(c->stream, c->ncell, c->nb, (const double*)c->M, c->empty_flag));
     c->empty_stale = false;
+    c->look_captured = c->look_captured || cap;
+    return LLGX_OK;
+}
+
+// A batch's samples are set one by one and looked at once, before the group's next
+// step (check_stepper).  Until then the flag is 1: a step that is replayed from the
+// caller's own graph passes no host code, and takes the test of every neighbour with
+// the same result.  One fill for all the samples set between two steps; under capture,
+// and once a look was captured, each copy brings its own, since the graph may run at
+// any time.
+static llgx_status note_new_state(Ctx* c) {
+    bool cap = false;
+    if (llgx_status st = capturing(c, &cap)) return st;
+    if (!c->empty_stale || cap || c->look_captured) HIPCHK(c, launch_fill_int(c->stream, c->empty_flag, 1, 1));
+    c->empty_stale = true;
     return LLGX_OK;
 }
 
@@ -2335,7 +2360,10 @@ static llgx_status batch_copy(llgx_batch b, int32_t i, const void* src, void* ds
         c->fsal_valid = false;
         c->abm_have_f = c->abm_have_prev = false;
         c->have_m = true;
-        c->empty_stale = true;  // one look at the whole group before its next step
+        if (e == hipSuccess && note_new_state(c) != LLGX_OK) {
+            bt->err = c->err;
+            return LLGX_E_HIP;
+        }
     } else {
         e = hipMemcpyAsync(dst_or_null, base, bytes, hipMemcpyDeviceToDevice, c->stream);
     }
