@@ -2145,14 +2145,48 @@ static llgx_status batch_step(Batch* bt, const llgx_stepper* s, llgx_step_info* 
 // step's end: 32 samples on four meshes 324 us a step (RK4 p = 4), 292 so.
 constexpr int GROUP_STEPS = 4;
 
+// after an error inside a call: groups left at different steps take none before
+// their samples are set again
+static void apart(Batch* bt) {
+    double t = bt->groups[0]->t;
+    bool same = true;
+    for (const Ctx* c : bt->groups) {
+        same = same && c->t == bt->groups[0]->t;
+        t = std::min(t, c->t);
+    }
+    if (same) return;
+    for (Ctx* c : bt->groups) {
+        c->t = t;
+        c->have_m = false;
+    }
+    bt->err += " (samples at different steps: set every sample again)";
+}
+
 template <typename T>
 static llgx_status run_groups(Batch* bt, const llgx_stepper* s, int64_t nsteps, int use_graph) {
+    if (nsteps <= 0) return LLGX_OK;
+    // every group before the first launch: a refused call leaves all of them at one time
+    bool cap = false;
+    for (Ctx* c : bt->groups) {
+        const Tableau* tab;
+        int p;
+        llgx_status st = check_stepper(c, s, &tab, &p);
+        if (st == LLGX_OK) st = capturing(c, &cap);
+        if (st) {
+            bt->err = c->err;
+            return st;
+        }
+    }
     Forked forked(bt);
     if (llgx_status st = forked.begin()) return st;
-    for (int64_t i = 0; i < nsteps; i += GROUP_STEPS)
+    // a stream that is being captured takes no graph of its own: the first group
+    // is refused where the others still stand at the same step
+    const int64_t turn = cap ? 1 : GROUP_STEPS;
+    for (int64_t i = 0; i < nsteps; i += turn)
         for (Ctx* c : bt->groups)
-            if (llgx_status st = do_run_fixed<T>(c, s, std::min<int64_t>(GROUP_STEPS, nsteps - i), use_graph, nullptr)) {
+            if (llgx_status st = do_run_fixed<T>(c, s, std::min(turn, nsteps - i), use_graph, nullptr)) {
                 bt->err = c->err;
+                apart(bt);
                 return st;
             }
     if (use_graph && !bt->groups[0]->graphs.empty()) {
