@@ -162,6 +162,7 @@ struct Ctx {
     long long n_exact = 0, n_extrap = 0, n_acc = 0, n_rej = 0, n_forced = 0;
 
     std::map<GraphKey, hipGraphExec_t> graphs;
+    long long n_replay = 0;     // graphs launched
 
     // When set, the launches of one step attempt are recorded here (kind of
     // the job-table batched kernel, its template count, its arguments)
@@ -1367,6 +1368,7 @@ static llgx_status do_run_fixed(Ctx* c, const llgx_stepper* s, int64_t nsteps, i
             it = c->graphs.emplace(key, ge).first;
         }
         HIPCHK(c, hipGraphLaunch(it->second, c->stream));
+        c->n_replay++;
         // the host side of the replayed steps
         for (int k = 0; k < nb; ++k) {
             const Plan pl = fixed_plan(c, tab, p, s->h);
@@ -2177,6 +2179,12 @@ static llgx_status run_groups(Batch* bt, const llgx_stepper* s, int64_t nsteps, 
             return st;
         }
     }
+    auto replays = [&] {
+        long long n = 0;
+        for (const Ctx* c : bt->groups) n += c->n_replay;
+        return n;
+    };
+    const long long before = replays();
     Forked forked(bt);
     if (llgx_status st = forked.begin()) return st;
     // a stream that is being captured takes no graph of its own: the first group
@@ -2189,7 +2197,7 @@ static llgx_status run_groups(Batch* bt, const llgx_stepper* s, int64_t nsteps, 
                 apart(bt);
                 return st;
             }
-    if (use_graph && !bt->groups[0]->graphs.empty()) {
+    if (replays() != before) {
         bt->last_jobs = 0;
         bt->last_kernels = -1;
     }
