@@ -11,6 +11,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <type_traits>
 #include <string>
 #include <vector>
@@ -1819,6 +1820,8 @@ struct Batch {
     std::vector<void*> tables;  // device job tables of the captured job-table steps
     std::vector<hipEvent_t> cap_events;  // fork/join events of the captured job-table steps
     int last_jobs = 0, last_kernels = 0;
+    // (method, order) of steps found to have no job-table form, which no other state decides
+    std::set<std::pair<int, int>> no_jobs;
 };
 
 // the streams and events of forked steps: ng - 1 side streams (default
@@ -2258,12 +2261,17 @@ static llgx_status batch_run_fixed(Batch* bt, const llgx_stepper* s, int64_t nst
             }
             continue;
         }
+        const std::pair<int, int> step{s->method, plans[0].p};
+        if (bt->no_jobs.count(step)) return run_groups<T>(bt, s, nsteps - i, use_graph);
         auto it = bt->graphs.find(keys);
         if (it == bt->graphs.end()) {
             hipGraphExec_t ge;
             int nk = 0;
             llgx_status st = capture_jobs<T>(bt, plans, &ge, &nk);
-            if (st == LLGX_E_UNSUPPORTED) return run_groups<T>(bt, s, nsteps - i, use_graph);
+            if (st == LLGX_E_UNSUPPORTED) {
+                bt->no_jobs.insert(step);
+                return run_groups<T>(bt, s, nsteps - i, use_graph);
+            }
             if (st) return st;
             it = bt->graphs.emplace(keys, ge).first;
             bt->last_jobs = 1;
