@@ -257,10 +257,12 @@ llgx_status llgx_profile_read(llgx_handle h, double ms[LLGX_K_COUNT], int64_t la
  * under the key (precision, spectral storage, mesh, sample count), so handles
  * created later with that key start with it.  us_out (may be NULL) receives
  * the chosen variants' fastest-round microseconds per launch (0 for a pass
- * the mesh does not need; on thin meshes the y passes are those of job-table
- * steps).  Needs llgx_precompute_demag and llgx_set_m (LLGX_E_STATE);
- * uses only the spectral workspace and the stage scratch array, so the
- * stepping state is unchanged.  Synchronises.
+ * the mesh does not need).  On thin meshes an evaluation is the x passes and
+ * ZMUL; the y passes are then those of job-table batch steps, timed with the
+ * tile that such steps take, and their variants are left as they are.  Needs
+ * llgx_precompute_demag and llgx_set_m (LLGX_E_STATE); uses only the spectral
+ * workspace and the stage scratch array, so the stepping state is unchanged.
+ * Synchronises.
  * llgx_time_passes: the same measurement for the current variants only.
  * llgx_get_variants / llgx_set_variants: read or force the choice
  * (LLGX_E_ARG for an index out of range).

@@ -416,13 +416,15 @@ static bool pass_exists(const Ctx* c, int kind) {
     return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && (c->Py == 1 || fused_yz(c)));
 }
 
-// passes that are timed and tuned: thin meshes' separate y passes too, which
-// job-table steps launch
-static bool pass_timed(const Ctx* c, int kind) {
-    return !((kind == LLGX_K_YFWD || kind == LLGX_K_YINV) && c->Py == 1);
+// The separate y passes of thin meshes are launched by job-table steps alone (spectra
+// in the working precision, lengths to 512), with these tiles (batch.hip): timed, but
+// there is nothing to choose.
+constexpr int JOB_Y_VARIANT = 1;
+static bool job_pass(const Ctx* c, int kind) {
+    return c->thin && c->spectral == LLGX_SPEC_NATIVE && c->Py <= 512 &&
+           (kind == LLGX_K_YFWD || kind == LLGX_K_YINV);
 }
 
-// launch one pass (kind LLGX_K_XFWD .. LLGX_K_XINV) with the handle's variant
 template <typename T, typename S>
 static llgx_status run_pass(Ctx* c, int kind, const EvalArgs<T>& a) {
     hipStream_t s = c->stream;
@@ -1607,7 +1609,13 @@ static llgx_status tune_ctx(Ctx* c, int reps, double us_out[5]) {
     for (int k = 0; k < 5; ++k) {
         te.var[k] = 0;
         te.us[k] = 0.0;
-        if (!pass_timed(c, k)) continue;
+        if (job_pass(c, k)) {
+            te.var[k] = c->var[k];
+            llgx_status st = time_pass_any(c, k, JOB_Y_VARIANT, reps, &te.us[k]);
+            if (st) return st;
+            continue;
+        }
+        if (!pass_exists(c, k)) continue;
         // the variants take turns over kTuneRounds rounds and each keeps its
         // fastest round, so a clock ramp or a burst of other work during one
         // variant's measurement does not decide the choice
@@ -2721,8 +2729,8 @@ llgx_status llgx_time_passes(llgx_handle h, int32_t reps, double us_out[5]) {
     if (!c->have_m) return c->fail(LLGX_E_STATE, "magnetization not set (llgx_set_m)");
     for (int k = 0; k < 5; ++k) {
         us_out[k] = 0.0;
-        if (!pass_timed(c, k)) continue;
-        llgx_status st = time_pass_any(c, k, c->var[k], reps, &us_out[k]);
+        if (!pass_exists(c, k) && !job_pass(c, k)) continue;
+        llgx_status st = time_pass_any(c, k, job_pass(c, k) ? JOB_Y_VARIANT : c->var[k], reps, &us_out[k]);
         if (st) return st;
     }
     return LLGX_OK;
