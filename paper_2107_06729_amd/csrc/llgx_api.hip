@@ -1541,44 +1541,69 @@ static std::string tune_key(const Ctx* c) {
 }
 
 // Variants a handle starts with (the tuner's choice for its key replaces them).
-// Every choice gives the same bits; the lines lie where the tiles of variant 0
-// (the widest that fill a workgroup) lost, microseconds per pass of variant 0
-// against the one chosen:
-//   x forward, FP32: 4 or 8 rows a tile up to LX = 256 (64x64x1 3.7 / 3.3,
-//     128x128x32 7.6 / 6.9, 256x256x16 10.9 / 10.8); longer rows only where that
-//     leaves fewer than 768 tiles (512x512x1 6.5 / 5.9; 300x300x20 18.6 / 22.6 the
-//     other way).  FP64: half tiles below 512 of them (256x64x1 4.7 / 4.3; 200x120x10
-//     8.6 / 9.7 the other way), double ones from LX = 320 on, whose rows were rounded
-//     down to a power of two (300x130x9 15.2 / 12.3, 512x512x64 405 / 293).
-//   x inverse: half tiles in FP32 (256x64x1 7.0 / 4.8, 256x256x16 14.2 / 12.7, BF16
-//     512x512x64 284 / 222; FP32 512x512x64 224 / 233 the other way); FP64 below 1024
-//     tiles (200x120x10 10.4 / 9.2; 128x128x32 13.2 / 14.0 the other way).
-//   y passes, spectra in the working precision: half-width tiles for FP32 lengths
-//     320 to 512 (256x256x16 16.5 / 14.9, 15.2 / 13.8; 256: level), FP64 256 to 512
-//     (300x130x9 27.4 / 15.6, 256x256x16 26.5 / 24.6); 16-bit rows of half a
-//     line lose (15.2 / 16.3).
-//   z pass: double tiles up to length 8 and at 24 (600x520x4 36.3 / 30.0, 300x300x12
-//     28.8 / 27.1), FP64 up to 16 (400x400x6 85.9 / 68.7); half ones for FP64 64
-//     (128x128x32 27.3 / 24.5).  The fused pass of thin meshes: yzy_default.
+// Every choice gives the same bits.  Lines from the pass times of all variants on
+// 2000 meshes drawn over the whole range of lengths and sizes (FP32, FP64 and BF16
+// spectra), checked on 1000 others: against variant 0, the widest tile that fills a
+// workgroup, the passes' geometric means are 0.94 (x forward), 0.92 (x inverse), 0.97
+// (y), 0.98 (z), no pass loses more than 0.5 us or 10 %; the best variant of each
+// would give 0.93, 0.91, 0.95, 0.96.
+//   x passes: half tiles (1) where variant 0 leaves CUs without work, so below a
+//     number of its tiles; above it they only idle threads (FP32 x inverse, rows of 8
+//     complex, 6893 tiles 12.1 / 20.0 us).  The number is higher where variant 0 needs
+//     a second round of threads (FP32 128, 192 and up: x inverse 256x256x16 14.2 / 12.7
+//     us, 128 always), lower where one stage of radix 10, 12 or 20 leaves few
+//     butterflies a row (80, 96, 160: FP64 160 1.5 to 2.2 times slower above 280 tiles)
+//     and for the shortest rows.  FP64 forward rows of 320 and more, which are one or
+//     two a tile: double tiles (2) above 1024 (20000 tiles of 320 / 512: 0.73 / 0.81 of
+//     variant 0; at 500 of 512 1.09); 640 above 4096 (500: 2.2, 5500: 0.66).
+//   y passes, spectra in the working precision: half tiles for FP32 lengths 320 to 512
+//     and FP64 256 to 512 while spectrum B fits half of the 256 MB cache (FP64 384:
+//     0.79 at 83 MB, 1.31 at 170 MB; 512: 0.96 at 119 MB, 1.07 at 134 MB; FP32 512: 0.92
+//     to 128 MB, 1.03 at 156 MB).
+//   z pass, by columns (kx, ky): double tiles for lengths up to 8 (FP32 from 16384
+//     columns: 9225 1.17, 17425 0.88), FP64 16 (4000 columns 0.96, before 1.05) and FP32
+//     24 (0.93 above 33000, 1.16 below 2200); FP64 24 stays (double 1.01 to 1.30: 200x120x10
+//     18.4 / 19.8 us); half tiles for FP64 64 on the same line as y (256x192x32, 160
+//     MB, 65.8 / 62.3 us, 256x256x32, 214 MB, 96.9 / 110).
+//   The fused pass of thin meshes: yzy_default.
 static void default_variants(Ctx* c) {
     const bool f32 = c->prec == LLGX_F32, native = c->spectral == LLGX_SPEC_NATIVE;
-    const long rows = 3L * c->ny * c->nz * c->nb, mesh_rows = (long)c->ny * c->nz * c->nb;
-    // rows of a variant-0 tile of the x passes
-    auto tile_rows = [&](int elems, int most) {
+    const int LX = c->LX;
+    const bool pow2 = (LX & (LX - 1)) == 0;
+    const long rows = (long)c->ny * c->nz * c->nb;
+    // tiles of variant 0 of the x passes
+    auto tiles = [&](long n, int elems, int most) {
         int r = 1;
-        while (2 * r * std::max(c->LX, 1) <= elems && 2 * r <= most) r *= 2;
-        return r;
+        while (2 * r * std::max(LX, 1) <= elems && 2 * r <= most) r *= 2;
+        return n / r;
     };
-    const long xf = rows / tile_rows(f32 ? 2048 : 1024, 16), xi = mesh_rows / tile_rows(f32 ? 1024 : 512, 8);
-    if (f32)
-        c->var[LLGX_K_XFWD] = c->LX <= 256 || xf < 768 ? 1 : 0;
-    else
-        c->var[LLGX_K_XFWD] = c->LX >= 320 ? 2 : xf < 512 ? 1 : 0;
-    c->var[LLGX_K_XINV] = f32 || xi < 1024 ? 1 : 0;
-    const int ylow = f32 ? 320 : 256;
-    c->var[LLGX_K_YFWD] = c->var[LLGX_K_YINV] = native && c->Py >= ylow && c->Py <= 512 ? 1 : 0;
-    if (c->thin) c->var[LLGX_K_ZMUL] = yzy_default(c->Py, c->nz, (long)c->Kx * c->nb);
-    if (!c->thin) c->var[LLGX_K_ZMUL] = c->Pz <= 8 || c->Pz == 24 || (!f32 && c->Pz == 16) ? 2 : !f32 && c->Pz == 64 ? 1 : 0;
+    const long xf = tiles(3 * rows, f32 ? 2048 : 1024, 16), xi = tiles(rows, f32 ? 1024 : 512, 8);
+    const long always = 1L << 40;
+    long half_f, half_i;  // half tiles below so many
+    if (f32) {
+        half_f = pow2 && LX >= 128 ? (LX <= 256 ? 4096 : 1024) : LX == 160 ? 192 : 512;
+        half_i = LX < 32 ? 0 : LX == 32 ? 128 : pow2 && LX >= 128 ? always : LX < 192 ? 256 : 1536;
+    } else {
+        half_f = LX < 24 ? 0 : LX == 80 || LX == 96 || LX == 160 || LX >= 320 ? 128 : 512;
+        half_i = LX < 16 ? 0 : LX < 32 || LX == 160 ? 128 : LX < 128 ? 256 : 768;
+    }
+    const bool double_f = !f32 && LX >= 320 && xf >= (LX == 640 ? 4096 : 1024);
+    c->var[LLGX_K_XFWD] = double_f ? 2 : xf < half_f ? 1 : 0;
+    c->var[LLGX_K_XINV] = xi < half_i ? 1 : 0;
+    const double bytes_b = 3.0 * c->nz * c->Py * c->SX * c->nb * (native ? 2 * (double)c->tsz : 4.0);
+    const bool b_fits = bytes_b < 128e6;
+    c->var[LLGX_K_YFWD] = c->var[LLGX_K_YINV] = native && c->Py >= (f32 ? 320 : 256) && c->Py <= 512 && b_fits ? 1 : 0;
+    const long cols = (long)c->Kx * c->Kyf * c->nb;
+    int z = 0;
+    if (c->thin)
+        z = yzy_default(c->Py, c->nz, (long)c->Kx * c->nb);
+    else if (c->Pz <= 8)
+        z = !f32 || !native || cols >= 16384 ? 2 : 0;
+    else if (c->Pz == (f32 ? 24 : 16))
+        z = cols >= (f32 ? 16384 : 4096) ? 2 : 0;
+    else if (!f32 && c->Pz == 64)
+        z = b_fits ? 1 : 0;
+    c->var[LLGX_K_ZMUL] = z;
 }
 
 static void drop_graphs(Ctx* c) {

@@ -37,11 +37,13 @@ bool yzy_ok(int LY, int nz, bool native) {
 }
 #if LLGX_INST == 0
 // Variant 0, but with 5 to 8 layers, more columns than CUs and two tiles in a CU's
-// LDS fewer threads, so that two tiles fit its registers as well (us: 200x120x6 17.8
-// / 13.0, 256x250x5 23.6 / 19.5, 400x128x8 29.6 / 23.9; one column a CU the other way,
-// 128x128x8 11.2 / 11.6, and so tiles that are alone in the LDS, 300x200x7 28.7 / 39.1).
+// LDS fewer threads, so that two tiles fit its registers as well (us, 120 rows of 6
+// layers: 257 columns 17.5 / 13.0, 321 18.3 / 13.9; 200 of 5: 257 22.1 / 18.5; one column
+// a CU the other way, 193 columns 10.3 / 10.8, 128x128x8 11.2 / 11.6, and so tiles that are
+// alone in the LDS, 300x200x7 28.7 / 39.1).
+constexpr int CUS = 256;
 int yzy_default(int LY, int nz, long columns) {
-    if (nz <= 4 || columns <= 256 || yzy_lds<float>(LY, nz, 1) > 80 * 1024) return 0;
+    if (nz <= 4 || columns <= CUS || yzy_lds<float>(LY, nz, 1) > 80 * 1024) return 0;
     return LY <= 256 ? 2 : 1;
 }
 template bool yzy_ok<float>(int, int, bool);
