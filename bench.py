@@ -115,7 +115,7 @@ def batch_step_bytes(problems, tsz, p, fused_ep=True):
         nx, ny, nz = n
         kx = (nx + 1 if nx > 1 else 1)
         kern = 6 * kx * ((ny + 1) if ny > 1 else 1) * ((nz + 1) if nz > 1 else 1) * tsz
-        if fused_ep and nz <= 4:
+        if fused_ep and nz <= (8 if tsz == 4 else 4):
             # one kernel for the y and z passes: spectrum A in and out
             kb.update(yfwd=0, yinv=0, zmul=2 * (kb["xfwd"] - 3 * nx * ny * nz * tsz) + kern)
         per = kb["xfwd"] + kb["yfwd"] + kb["zmul"] + kb["yinv"] + kb["xinv"] + kb["epoly"] \

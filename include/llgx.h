@@ -207,8 +207,10 @@ llgx_status llgx_step(llgx_handle h, const llgx_stepper* s, llgx_step_info* info
 /* nsteps fixed steps (s->adaptive must be 0) with no host synchronisation;
  * with use_graph the steady-state steps are captured into HIP graphs (per
  * history phase; 8 consecutive steps per graph while at least 8 remain,
- * else one) and replayed, bitwise the same as eager steps.  info (the last
- * step's) may be NULL; its max_dmdt is -1. */
+ * else one) and replayed: the same launches as eager steps, with the Eq. (6)
+ * weights of the captured step (those of an eager step can differ from them
+ * in FP64's last bit, by the rounding of t).  info (the last step's) may be
+ * NULL; its max_dmdt is -1. */
 llgx_status llgx_run_fixed(llgx_handle h, const llgx_stepper* s, int64_t nsteps, int32_t use_graph,
                            llgx_step_info* info);
 
@@ -308,12 +310,16 @@ llgx_status llgx_load_state(llgx_handle h, const void* host_buf, size_t len);
  * field sweeps) stepped together.  Samples whose problems are equal except
  * for Ha share one set of kernels: every launch covers all of them (FFT
  * passes over all their rows, per-sample applied fields).  With use_graph,
- * one steady-state step of all samples is captured into a HIP graph (one per
- * history phase) and replayed.  All samples share the stepper and the
- * time: adaptive steps (llgx_batch_step) take one h for all.  spectral: the spectra's storage, as for
- * llgx_create (16-bit storage requires LLGX_F32).  llgx_batch_set_m on any
+ * each group's steady-state steps are captured into HIP graphs of one step
+ * (one per history phase) and replayed (LLGX_BATCH_JOBS: one graph for all
+ * groups).  All samples share the stepper and the time: adaptive steps
+ * (llgx_batch_step) take one h for all.  spectral: the spectra's storage, as
+ * for llgx_create (16-bit storage requires LLGX_F32).  llgx_batch_set_m on any
  * sample restarts priming of its group.  Per-sample M is [3][nz][ny][nx] of
- * the batch precision. */
+ * the batch precision.
+ * llgx_batch_run_fixed checks every group before it steps any: a refused call
+ * leaves all samples as they are.  An error inside it (HIP) that leaves the
+ * groups at different times refuses steps until the samples are set again. */
 typedef struct llgx_batch_s* llgx_batch;
 llgx_status llgx_batch_create(int32_t n, const llgx_problem* problems, int32_t precision, int32_t spectral,
                               void* hip_stream, llgx_batch* out);
@@ -347,19 +353,20 @@ llgx_status llgx_batch_info(llgx_batch b, int32_t* ngroups, int64_t* total_cells
  *     The job tables live in device memory the batch allocates when it
  *     captures a step and frees in llgx_batch_destroy.  Steps that have no
  *     job-table form (16-bit spectra, padded lengths above 1024 along x,
- *     512 along y or 64 along z) are captured as with LLGX_BATCH_STREAMS.
+ *     512 along y or 64 along z) are stepped as with LLGX_BATCH_STREAMS.
  *   LLGX_BATCH_STREAMS (default): each group's own launches and graphs, on
  *     streams forked from the batch stream for the whole call, so the
  *     kernels of different meshes overlap, and a small mesh's step does not
  *     wait at every pass for the large ones (the faster of the two on the
  *     64-sample sweep of four meshes).
  * Both give each sample the bits it gets when stepped alone.  Changing the
- * mode synchronises the batch stream and drops the captured graphs.
- * LLGX_E_ARG for an unknown mode.
- * llgx_batch_launch_info: whether the graph captured last uses job tables
- * (1) or forked streams (0), and its job-table launches per step (-1 when
- * forked); when a step falls back to forked streams, llgx_batch_last_error
- * says why. */
+ * mode synchronises the batch stream and drops the job-table graphs (the
+ * groups keep their own).  LLGX_E_ARG for an unknown mode.
+ * llgx_batch_launch_info: which came later, the capture of a job-table step
+ * (1) or a replay of the groups' own graphs (0), and the former's launches per
+ * step (-1 for the latter); calls that replay nothing leave it.  When a step
+ * is found to have no job-table form, llgx_batch_last_error says why (once
+ * per method and order). */
 #define LLGX_BATCH_JOBS 0
 #define LLGX_BATCH_STREAMS 1
 llgx_status llgx_batch_set_launch(llgx_batch b, int32_t mode);

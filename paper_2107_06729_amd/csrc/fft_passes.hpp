@@ -31,9 +31,9 @@ constexpr int NT = 256;
 
 // ------------------------------------------------------------------------
 // Tile choices (LDS budget per workgroup).  Every pass has launch variants
-// (tile widths or rows per workgroup) that compute bit-identical results;
-// variant 0 is the default and the autotuner picks among the others by
-// timing them on the problem's own shapes.
+// (tile widths or rows per workgroup) that compute bit-identical results.  A
+// handle starts with those of default_variants (llgx_api.hip); the autotuner
+// picks among all of them by timing them on the problem's own shapes.
 template <typename T>
 constexpr int col_tile(int L, int v) {
     const int t = sizeof(T) == 4 ? (L <= 512 ? 16 : 8) : (L <= 512 ? 8 : 4);

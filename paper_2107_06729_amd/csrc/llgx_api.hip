@@ -128,7 +128,7 @@ struct Ctx {
     double* parts = nullptr;
     int nparts = 1;             // blocks of the 1-D reduction kernels
     long nparts_alloc = 1;      // capacity of parts (also covers the 2-D cell grid)
-    double* scal = nullptr;     // [0] error norm, [1..3] sums for <M>
+    double* scal = nullptr;     // [1..3] sums for <M>, [4] max |dM/dt|
     double* err_host = nullptr; // partial maxima of the error estimate in pinned host memory (adaptive
     double* err_dev = nullptr;  // steps, ERR_SLOTS), their device address, and how many of them the
     int err_n = 0;              // latest attempt writes
@@ -1844,11 +1844,11 @@ struct Batch {
     std::vector<hipStream_t> gstreams;
     std::vector<hipEvent_t> joins;
     hipEvent_t fork = nullptr;
-    // LLGX_BATCH_STREAMS (default): the groups' own launches on forked
-    // streams; LLGX_BATCH_JOBS: each pass of a captured step is one
+    // LLGX_BATCH_STREAMS (default): the groups' own launches and graphs on
+    // forked streams; LLGX_BATCH_JOBS: each pass of a captured step is one
     // launch over a job table of the mesh groups (per FFT length
     // for the FFT passes; up to BMAX groups a launch), where every launch of
-    // the step has that form (else the forked-stream capture)
+    // the step has that form (else the groups' own, as with LLGX_BATCH_STREAMS)
     int mode = LLGX_BATCH_STREAMS;
     std::vector<void*> tables;  // device job tables of the captured job-table steps
     std::vector<hipEvent_t> cap_events;  // fork/join events of the captured job-table steps
@@ -1932,7 +1932,7 @@ static bool same_material(const llgx_problem& a, const llgx_problem& b) {
 // lifetime), and the launches are captured on the batch stream, those of
 // one pass side by side on forked streams.  LLGX_E_UNSUPPORTED (nothing
 // captured) when some launch has no job-table form or the groups' launch
-// sequences differ (then the forked-stream capture is used).
+// sequences differ (then the groups step on their own, run_groups).
 template <typename T>
 static llgx_status capture_jobs(Batch* bt, const std::vector<Plan>& plans, hipGraphExec_t* out, int* nkern) {
     const size_t ng = bt->groups.size();

@@ -21,7 +21,8 @@
 // (RowFFT's layout); the z transform of a (column, ky) is in one thread's
 // registers, and its three components meet there for the product.
 // The arithmetic is that of ColFFT and zmul_tile, operation for operation, with
-// 16-bit spectra rounded where the separate passes store them: the same bits.
+// 16-bit spectra rounded where the separate passes store them: the same bits, but for
+// FP32 at LY = 1024, where ColFFT starts with radix 16 (col_radix) and RowFFT with 2.
 #pragma once
 #include <hip/hip_runtime.h>
 
